@@ -279,7 +279,8 @@ typedef struct pdec_plan_info {
     int32_t path;          /* 1 = vector kernel, 2 = matrix-core kernel                          */
     int32_t kernel_shape;  /* matrix-core work-group shape: 1 = 64 rows, 2 = 128 rows,          */
                            /* 3 = 256 rows on 16-row tiles; 4 = 256 rows, 5 = 128 rows on      */
-                           /* 32-row tiles (pdec_set_path(3) only); 0 on the vector path       */
+                           /* 32-row tiles (pdec_set_path(3) only); whole branches: 6 = 128     */
+                           /* rows, 7 = 256 rows; 0 on the vector path                          */
     int32_t rows_per_item; /* query rows of one kv head that one work item serves               */
     int32_t row_groups;    /* work items per (video, kv head, chunk): ceil(rows / rows_per_item)  */
     int32_t chunk_keys;    /* keys of the virtual key sequence per chunk                         */

@@ -39,14 +39,16 @@ constexpr int kMaxChunks = 512;  // largest slot count per row the host plans
 
 typedef __attribute__((ext_vector_type(4))) uint32_t fin_u32x4_t;
 
-template <typename T, int D, bool EARLY>
+// SLOTS: slots per batch.  A few-slot row (whole branches) would spend most
+// of a 64-slot batch on clamped re-reads of its last slot.
+template <typename T, int D, bool EARLY, int SLOTS = 64>
 __global__ __launch_bounds__(256) void finish_kernel(StepArgs a)
 {
     using u32x4_t = fin_u32x4_t;
     constexpr int EPL = 16 / (int)sizeof(T);  // elements per lane and slot
     constexpr int LPS = D / EPL;              // lanes per slot
     constexpr int SPI = 64 / LPS;             // slots per wave instruction
-    constexpr int NB = 64 / SPI < 16 ? 64 / SPI : 16;  // slots per lane and batch
+    constexpr int NB = SLOTS / SPI < 16 ? SLOTS / SPI : 16;  // slots per lane and batch
     constexpr int BATCH = SPI * NB;
     static_assert(LPS * EPL == D && SPI * LPS == 64, "head_dim 64 or 128");
 

@@ -86,19 +86,15 @@ __device__ inline float max_over_groups(float x)
 constexpr float kMinRef = -1e30f;
 
 
-template <int D, int NT, int WR, int WK, bool MQ>
+template <int D, int NT, int WR, int WK>
 struct MfmaCfg {
     static constexpr int NW = WR * WK;            // waves
     static constexpr int KS = kUnit;              // keys per stage: one unit
     static constexpr int KW = KS / WK;            // keys per key group per stage
-    // Ring slots.  A decode step keeps two stages in flight while the third
-    // is consumed (a ring probe streams the decode layout as fast with two
-    // stages in flight as with three or four) and stages its query rows by
-    // DMA (QDMA); whole branches, whose items run many matrix-bound stages,
-    // keep three in flight and load their query rows directly (measured
-    // faster: the prefill call 649 against 700 us).
-    static constexpr bool QDMA = !MQ;
-    static constexpr int NSTAGE = QDMA ? 3 : 4;
+    // Ring slots: two stages in flight while the third is consumed (a ring
+    // probe streams the decode layout as fast with two stages in flight as
+    // with three or four); the query rows are staged by DMA, ahead of them.
+    static constexpr int NSTAGE = 3;
     static constexpr int ROWB = D * 2;            // bytes per key row
     static constexpr int CH = D / 8;              // 16-byte chunks per key row
     static constexpr int STAGE_K = KS * ROWB;     // bytes of K per stage
@@ -120,7 +116,7 @@ struct MfmaCfg {
     // (SR bytes), and the rest in an area of their own (XR bytes per wave).
     static constexpr int QB = NT * 16 * ROWB;
     static constexpr int SR = STAGE / NW;
-    static constexpr int XR = QDMA ? QB - SR : 0;
+    static constexpr int XR = QB - SR;
     static constexpr int QX = NW * XR;
     static_assert(XR >= 0 && SR % 1024 == 0 && XR % 1024 == 0, "query staging");
     // A tail work-group's eight waves each stage a 32-key K and V block
@@ -295,29 +291,25 @@ __device__ inline void tail_pair(const StepArgs& a, uint32_t buf, int pair)
     if (lg == 0) *reinterpret_cast<float2*>(a.part_ml + 2 * slot) = make_float2(m_ref, l);
 }
 
-template <int D, int NT, int WR, int WK, bool PLAN, bool MQ>
+template <int D, int NT, int WR, int WK, bool PLAN>
 __global__ __launch_bounds__(64 * WR * WK) void split_mfma_kernel(StepArgs a)
 {
-    using C = MfmaCfg<D, NT, WR, WK, MQ>;
+    using C = MfmaCfg<D, NT, WR, WK>;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[C::LDS];
     __shared__ __attribute__((aligned(1024))) unsigned char qx[C::QXA];
     __shared__ int tab_start[kMaxStreamsPerVideo + 1];
     __shared__ int tab_nlen[kMaxStreamsPerVideo];
     __shared__ int s_total;
 
-    if constexpr (!MQ) {
-        // per-stream tail pass (decode steps only; the kernels of whole
-        // branches carry none of its code): waves 0..7, one (stream, kv
-        // head) pair each
-        if ((int)blockIdx.x < a.tail_blocks) {
-            const int w = threadIdx.x >> 6;
-            const int pair = (int)blockIdx.x * 8 + w;
-            if (w < 8 && pair < a.num_events * a.H_kv) {
-                const int off = w * 2 * C::TVB;
-                tail_pair<D>(a, off < C::LDS ? lds_u32(lds + off) : lds_u32(qx + (off - C::LDS)), pair);
-            }
-            return;
+    // per-stream tail pass: waves 0..7, one (stream, kv head) pair each
+    if ((int)blockIdx.x < a.tail_blocks) {
+        const int w = threadIdx.x >> 6;
+        const int pair = (int)blockIdx.x * 8 + w;
+        if (w < 8 && pair < a.num_events * a.H_kv) {
+            const int off = w * 2 * C::TVB;
+            tail_pair<D>(a, off < C::LDS ? lds_u32(lds + off) : lds_u32(qx + (off - C::LDS)), pair);
         }
+        return;
     }
 
     // ---- which item; every branch below is uniform over the work-group ----
@@ -366,19 +358,7 @@ __global__ __launch_bounds__(64 * WR * WK) void split_mfma_kernel(StepArgs a)
         if (app_store) fused_append_store(a, vi, id.g, 2);
         return;
     }
-    int nstages = u1 - u0;
-    if constexpr (MQ) {
-        // whole branches: rows of one stream f see none of the units after
-        // f's unit holding their largest token (other streams' units are
-        // hidden without the causal-attention variant).  The item still
-        // writes its partial state, empty if no stage is left.
-        const int per = a.G * a.qps;
-        const int f = row0 / per;
-        if (!a.cross && (row0 + nrows - 1) / per == f && u1 > upre) {
-            const int tok_hi = ((row0 + nrows - 1) / a.G) % a.qps;
-            nstages = max(0, min(nstages, upre + tab_start[f] + tok_hi / kUnit + 1 - u0));
-        }
-    }
+    const int nstages = u1 - u0;
 
     const uint16_t* __restrict__ kpre = static_cast<const uint16_t*>(a.k_prefix);
     const uint16_t* __restrict__ vpre = static_cast<const uint16_t*>(a.v_prefix);
@@ -442,7 +422,7 @@ __global__ __launch_bounds__(64 * WR * WK) void split_mfma_kernel(StepArgs a)
     // from its first row and zeroed after the read.
     unsigned char* const qslot = lds + (C::NSTAGE - 1) * C::STAGE + w * C::SR;
     unsigned char* const qext = qx + w * C::XR;
-    const bool q_dma = C::QDMA && row_wave_active && nstages > 0;
+    const bool q_dma = row_wave_active && nstages > 0;
     if (q_dma) {
         const uint16_t* __restrict__ q = static_cast<const uint16_t*>(a.q);
 #pragma unroll
@@ -460,55 +440,12 @@ __global__ __launch_bounds__(64 * WR * WK) void split_mfma_kernel(StepArgs a)
         if (st < nstages) issue_stage(st);
 
     int lane_stream[NT];
-    int lane_tok[NT];  // query token of the row within its stream (whole branches; 0 otherwise)
     bf16x8_t qf[NT][C::KSTEPS];  // Q^T operands: q[row][32t + 8lg .. +7]
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         const int r = 16 * (rw * NT + nt) + l16;
         const bool ok = r < nrows;
         lane_stream[nt] = ok ? (row0 + r) / (a.G * a.qps) : -2;
-        lane_tok[nt] = ok ? ((row0 + r) / a.G) % a.qps : 0;
-        if constexpr (!C::QDMA) {
-            // direct loads, awaited with every stage in flight (plain loads
-            // and DMA share one counter and complete out of order)
-            const uint16_t* __restrict__ q = static_cast<const uint16_t*>(a.q);
-            const long base = ok ? (long)row_qrow(a, vi, id.g, row0 + r) * D : 0;
-#pragma unroll
-            for (int t = 0; t < C::KSTEPS; ++t) {
-                u32x4_t x = {0u, 0u, 0u, 0u};
-                if (ok) x = *reinterpret_cast<const u32x4_t*>(q + base + 32 * t + 8 * lg);
-                qf[nt][t] = as_bf16x8(x);
-            }
-        }
-    }
-    if constexpr (!C::QDMA) wait_vmcnt<0>();
-
-    // Whole branches: the range of query tokens and streams among this
-    // wave's rows (uniform over the wave).  No row sees an own key above the
-    // largest token, and an own unit that lies below the smallest token of a
-    // wave whose rows all belong to its stream is seen whole by every row.
-    int w_tok_lo = 0x7fffffff, w_tok_hi = -1, w_str_lo = 0x7fffffff, w_str_hi = -1;
-    if constexpr (MQ) {
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            if (lane_stream[nt] >= 0) {
-                w_tok_lo = min(w_tok_lo, lane_tok[nt]);
-                w_tok_hi = max(w_tok_hi, lane_tok[nt]);
-                w_str_lo = min(w_str_lo, lane_stream[nt]);
-                w_str_hi = max(w_str_hi, lane_stream[nt]);
-            }
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            w_tok_lo = min(w_tok_lo, __shfl_xor(w_tok_lo, off));
-            w_tok_hi = max(w_tok_hi, __shfl_xor(w_tok_hi, off));
-            w_str_lo = min(w_str_lo, __shfl_xor(w_str_lo, off));
-            w_str_hi = max(w_str_hi, __shfl_xor(w_str_hi, off));
-        }
-        w_tok_lo = __builtin_amdgcn_readfirstlane(w_tok_lo);
-        w_tok_hi = __builtin_amdgcn_readfirstlane(w_tok_hi);
-        w_str_lo = __builtin_amdgcn_readfirstlane(w_str_lo);
-        w_str_hi = __builtin_amdgcn_readfirstlane(w_str_hi);
     }
 
     // The row normaliser is one more matrix product per block, ones^T P^T:
@@ -585,16 +522,7 @@ __global__ __launch_bounds__(64 * WR * WK) void split_mfma_kernel(StepArgs a)
                         const bool kout = kb + 16 * kt + 4 * lg + i >= ui.nk;
 #pragma unroll
                         for (int nt = 0; nt < NT; ++nt) {
-                            bool hide;
-                            if constexpr (MQ) {
-                                // whole branches: query j sees its own rows 0 .. j; with the
-                                // causal-attention variant also other streams' rows 0 .. j-1
-                                const bool other = lane_stream[nt] != ui.stream;
-                                const int lim = other ? (a.cross ? lane_tok[nt] - 1 : -1) : lane_tok[nt];
-                                hide = kout || (ui.stream >= 0 && ui.k0 + kb + 16 * kt + 4 * lg + i > lim);
-                            } else {
-                                hide = kout || (ui.stream >= 0 && lane_stream[nt] != ui.stream);
-                            }
+                            const bool hide = kout || (ui.stream >= 0 && lane_stream[nt] != ui.stream);
                             if (hide) s[kt][nt][i] = kNegInf;
                         }
                     }
@@ -655,10 +583,9 @@ __global__ __launch_bounds__(64 * WR * WK) void split_mfma_kernel(StepArgs a)
     for (int st = 0; st < nstages; ++st) {
         // after the barrier every wave's pieces of stage st have landed and
         // stage st-1 has been consumed, so its buffer can be refilled
-        if (C::NSTAGE >= 4 && st + 2 < nstages) stage_barrier<2 * C::DMA_PER_WAVE>();
-        else if (st + 1 < nstages) stage_barrier<C::DMA_PER_WAVE>();
+        if (st + 1 < nstages) stage_barrier<C::DMA_PER_WAVE>();
         else stage_barrier<0>();
-        if (C::QDMA && st == 0) {
+        if (st == 0) {
             // the wave's query rows have landed (they precede stage 0 on its
             // counter): read the Q^T operands before this wave's DMA below
             // refills their part of the ring
@@ -681,19 +608,11 @@ __global__ __launch_bounds__(64 * WR * WK) void split_mfma_kernel(StepArgs a)
         const UnitInfo ui = unit_info(a, vi, upre, tab_start, tab_nlen, id.g, u0 + st);
         // an own unit of stream f only concerns the rows of f
         bool wave_has_rows = row_wave_active;
-        if (ui.stream >= 0 && !(MQ && a.cross)) {
+        if (ui.stream >= 0) {
             const int f0 = ui.stream * a.G * a.qps, f1 = f0 + a.G * a.qps;  // video rows of stream f
             wave_has_rows = wave_has_rows && f0 < wrow0 + 16 * NT && f1 > wrow0;
         }
-        bool whole = ui.stream < 0 && ui.nk == kUnit && (!PLAN || ui.k0 + kUnit <= vi.plan0);
-        if constexpr (MQ) {
-            if (ui.stream >= 0) {
-                // own keys t are seen at most by rows whose token is >= t
-                if (ui.k0 > w_tok_hi) wave_has_rows = false;
-                whole = ui.nk == kUnit && w_str_lo == ui.stream && w_str_hi == ui.stream &&
-                        ui.k0 + kUnit - 1 <= w_tok_lo;
-            }
-        }
+        const bool whole = ui.stream < 0 && ui.nk == kUnit && (!PLAN || ui.k0 + kUnit <= vi.plan0);
         const unsigned char* kbuf = lds + (st % C::NSTAGE) * C::STAGE;
         const unsigned char* vbuf = kbuf + C::STAGE_K;
         if (wave_has_rows) {

@@ -103,6 +103,8 @@ struct Plan {
     int max_chunks;     // slots per row: the tail slot (slot0 = 1) and the chunks
     int tail_blocks;    // work-groups of the per-stream tail pass (0: own units in the items)
     int slot0;          // slot of chunk 0
+    int own_bound;      // whole branches: own units that one row group may see
+    bool rows_first;    // whole branches: item order (kernel_branch.h)
     long n_items;
     size_t part_o_bytes;  // normalised partial outputs
     size_t part_ml_bytes; // (max, normaliser) pairs
@@ -149,13 +151,80 @@ int validate_dims(const pdec_dims* d, int num_videos)
     return PDEC_OK;
 }
 
-Plan make_plan(const pdec_dims* d, int num_videos)
+// Workspace layout for p.max_chunks slots per row.
+void size_workspace(const pdec_dims* d, int num_videos, Plan* p)
+{
+    const size_t rows = (size_t)d->num_events * d->num_q_heads * std::max(d->queries_per_stream, 1);
+    const size_t elem = d->dtype == PDEC_DTYPE_BF16 ? 2 : 4;
+    p->part_o_bytes = (size_t)p->max_chunks * rows * d->head_dim * elem;  // a multiple of 128 bytes
+    p->part_ml_bytes = (size_t)p->max_chunks * rows * 2 * sizeof(float);
+    p->ws_bytes = p->part_o_bytes + p->part_ml_bytes + (size_t)num_videos * sizeof(int32_t);
+}
+
+// Whole branches (kernel_branch.h).  A row group of 256 rows (128 when a
+// video has no more) sees the prefix units and the own units of the streams
+// its rows belong to; the chunk count is the one with the least estimated
+// time: the rounds its items take on the compute units, each an item's units
+// plus a fixed cost, and the finish pass over the slots.
+Plan make_branch_plan(const pdec_dims* d, int num_videos)
 {
     Plan p{};
     const int G = d->num_q_heads / d->num_kv_heads;
     const int ev = events_per_video(d);
-    const int qps = std::max(d->queries_per_stream, 1);
-    const long rows_max = (long)ev * G * qps;  // query rows per (video, kv head)
+    const long N = d->queries_per_stream;
+    const long per = N * G, rows_max = ev * per;
+    p.path = kPathMfma;
+    p.rows_per_item = rows_max > 128 ? 256 : 128;
+    p.shape = rows_max > 128 ? 7 : 6;
+    p.rg_max = (int)ceil_div(rows_max, p.rows_per_item);
+    // own units of one row group: every stream but the last it touches may be
+    // seen whole, the last up to the group's tokens of it
+    const long full = ceil_div(std::min<long>(d->event_cap, N), kUnitKeys);
+    long own = full * ev;
+    if (!d->cross_causal) {
+        const long spans = std::min<long>(ev, (p.rows_per_item - 2) / per + 2);
+        const long last = std::min(full, ceil_div(p.rows_per_item / G + 2, kUnitKeys));
+        if (spans >= 2) own = (spans - 1) * full + last;
+        else own = full;
+    }
+    const long upre = ceil_div(d->max_prefix_len, kUnitKeys), units = std::max<long>(upre + own, 1);
+    p.own_bound = (int)std::min<long>(own, 1L << 24);
+    p.rows_first = num_videos > 1 || own > upre;
+    const long tokens = d->prefix_tokens > 0 ? d->prefix_tokens : (long)num_videos * d->max_prefix_len;
+    const double rows = (double)d->num_events * d->num_q_heads * N;
+    // a stream's rows see half of its units on average
+    const double mean_units = (double)tokens / num_videos / kUnitKeys + (d->cross_causal ? own : 0.5 * own);
+    const double unit_us = p.rows_per_item == 256 ? 1.4 : 0.9, fixed_units = 4.0;
+    double best = 0.0;
+    long chunks = 1;
+    for (long n = 1; n <= std::min<long>(units, kMaxChunks); ++n) {
+        if (n > 1 && n * rows * (d->head_dim * 2 + 8) + num_videos * 4.0 > (double)PDEC_NOALLOC_SCRATCH_BYTES) break;
+        const long upc = ceil_div(units, n);
+        if (ceil_div(units, upc) != n) continue;  // fewer chunks of the same length do
+        const double items = (double)num_videos * d->num_kv_heads * p.rg_max * n;
+        double t = p.rows_first ? std::max(upc + fixed_units, items * (mean_units / n + fixed_units) / kTargetItems)
+                                : std::ceil(items / kTargetItems) * (upc + fixed_units);
+        t *= unit_us;
+        if (n > 1) t += 4.0 + rows * n * (d->head_dim * 2 + 8) / 4.0e6;
+        if (n == 1 || t < best) {
+            best = t;
+            chunks = n;
+        }
+    }
+    p.unit_per_chunk = (int)std::min<long>(ceil_div(units, chunks), 1L << 24);
+    p.max_chunks = (int)ceil_div(units, p.unit_per_chunk);
+    p.n_items = (long)num_videos * d->num_kv_heads * p.max_chunks * p.rg_max;
+    size_workspace(d, num_videos, &p);
+    return p;
+}
+
+Plan make_plan(const pdec_dims* d, int num_videos)
+{
+    if (d->queries_per_stream > 1) return make_branch_plan(d, num_videos);
+    Plan p{};
+    const int G = d->num_q_heads / d->num_kv_heads;
+    const int ev = events_per_video(d);
+    const long rows_max = (long)ev * G;  // query rows per (video, kv head)
     // bf16 runs on the matrix cores at any row count: a single-stream step
     // (7 rows per kv head) pads its 16-row tile and still takes about half
     // the time of the vector kernel (12.8 vs 22.7 us at a 16384-token
@@ -164,14 +233,13 @@ Plan make_plan(const pdec_dims* d, int num_videos)
     const int ov = g_path_override.load();
     if (ov == kPathValu) path = kPathValu;
     if ((ov == kPathMfma || ov == kPathMfma32) && d->dtype == PDEC_DTYPE_BF16) path = kPathMfma;
-    if (qps > 1) path = kPathMfma;  // the vector kernels take one query per stream
     p.path = path;
     if (path == kPathMfma) {
         // up to 4 tiles of 16 rows -> 8 waves: 1 tile per row wave, 2 key
         // groups (64 rows); up to 8 -> 128 rows: 16 waves of one tile x 2
-        // key groups (decode step, D = 128) or 8 waves of 2 tiles x 2 key
-        // groups; more -> 256 rows per item: 16 one-tile row waves (decode
-        // step, D = 128) or 8 two-tile row waves (whole branches, D = 64).  On request the decode step at D = 128 with
+        // key groups (D = 128) or 8 waves of 2 tiles x 2 key groups; more ->
+        // 256 rows per item: 16 one-tile row waves (D = 128) or 8 two-tile row
+        // waves (D = 64).  On request the decode step at D = 128 with
         // more than 64 rows runs on 32-row tiles instead (128 rows as 4 row
         // waves x 2 key groups, 256 rows as 8 row waves): half the LDS
         // operand reads, but two waves per SIMD, which hide the memory path
@@ -179,7 +247,7 @@ Plan make_plan(const pdec_dims* d, int num_videos)
         const long tiles = ceil_div(rows_max, 16);
         p.shape = tiles <= 4 ? 1 : tiles <= 8 ? 2 : 3;
         p.rows_per_item = tiles <= 4 ? 64 : tiles <= 8 ? 128 : 256;
-        if (ov == kPathMfma32 && d->head_dim == 128 && qps == 1 && p.shape > 1) p.shape = p.shape == 2 ? 5 : 4;
+        if (ov == kPathMfma32 && d->head_dim == 128 && p.shape > 1) p.shape = p.shape == 2 ? 5 : 4;
     } else {
         p.shape = 0;
         p.rows_per_item = 8;
@@ -192,11 +260,7 @@ Plan make_plan(const pdec_dims* d, int num_videos)
     const long own_units_max = (long)ev * ceil_div(d->event_cap, kUnitKeys);
     const long units_max = ceil_div(d->max_prefix_len, kUnitKeys) + own_units_max;
     const long tokens = d->prefix_tokens > 0 ? d->prefix_tokens : (long)num_videos * d->max_prefix_len;
-    // a decode step's streams hold about one unit each; whole branches hold
-    // up to min(cap, Q) rows each (one stream with an empty prefix and the
-    // prefix as its rows is plain causal attention over it)
-    const long own_expected = qps > 1 ? (long)d->num_events * ceil_div(std::min<long>(d->event_cap, qps), kUnitKeys)
-                                      : (long)d->num_events;
+    const long own_expected = d->num_events;  // a decode step's streams hold about one unit each
     const long units_expected = ceil_div(tokens, kUnitKeys) + own_expected;
     long upc = ceil_div(units_expected * d->num_kv_heads * p.rg_max, kTargetItems);
     if (path == kPathValu) {
@@ -220,7 +284,7 @@ Plan make_plan(const pdec_dims* d, int num_videos)
     // items; a long cache (a single stream decoding alone, say) stays spread
     // over the chunks as units.  A one-chunk step keeps its own units in the
     // item, which then writes the result without a finish pass.
-    if (path == kPathMfma && qps == 1 && G <= 16 && p.shape <= 3 && p.max_chunks > 1) {
+    if (path == kPathMfma && G <= 16 && p.shape <= 3 && p.max_chunks > 1) {
         const long pairs = (long)d->num_events * d->num_kv_heads;
         const long tb = 8 * ceil_div(ceil_div(pairs, kTailPairs), 8);
         const long target = std::max<long>(kTargetItems - tb, kTargetItems / 2);
@@ -236,11 +300,7 @@ Plan make_plan(const pdec_dims* d, int num_videos)
         }
     }
     p.n_items = (long)num_videos * d->num_kv_heads * (p.max_chunks - p.slot0) * p.rg_max;
-    const size_t rows = (size_t)d->num_events * d->num_q_heads * std::max(d->queries_per_stream, 1);
-    const size_t elem = d->dtype == PDEC_DTYPE_BF16 ? 2 : 4;
-    p.part_o_bytes = (size_t)p.max_chunks * rows * d->head_dim * elem;  // a multiple of 128 bytes
-    p.part_ml_bytes = (size_t)p.max_chunks * rows * 2 * sizeof(float);
-    p.ws_bytes = p.part_o_bytes + p.part_ml_bytes + (size_t)num_videos * sizeof(int32_t);
+    size_workspace(d, num_videos, &p);
     return p;
 }
 
@@ -340,6 +400,12 @@ struct FusedAppend {
     int32_t* lens_out;
 };
 
+template <int D, int SLOTS>
+void launch_branch_finish(const StepArgs& a, int grid, hipStream_t s)
+{
+    hipLaunchKernelGGL((finish_kernel<uint16_t, D, false, SLOTS>), dim3(grid), dim3(256), 0, s, a);
+}
+
 // One-video calls issue the first batch of a row's slots before its counts
 // (kernel_finish.h); a ragged batch waits for them.
 template <bool EARLY>
@@ -432,7 +498,9 @@ int run_step(const pdec_dims* d, int num_videos, const void* q, const void* k_pr
     hipEvent_t ev_start, ev_stop;
     timer_slot_events(&ev_start, &ev_stop);
     if (ev_start && hipEventRecord(ev_start, s) != hipSuccess) return PDEC_ERR_HIP;
-    if (p.path == kPathMfma) {
+    if (a.qps > 1) {
+        launch_branch(a, p.own_bound, p.rows_first, s);
+    } else if (p.path == kPathMfma) {
         launch_split_mfma(a, p.shape, grid, s);
     } else if (bf16) {
         if (d->head_dim == 128) launch_valu<uint16_t, 128>(a, grid, s);
@@ -446,8 +514,22 @@ int run_step(const pdec_dims* d, int num_videos, const void* q, const void* k_pr
     // one chunk per row on the matrix-core path: the split pass wrote the result
     if (p.path == kPathMfma && p.max_chunks == 1) return PDEC_OK;
     const int fgrid = (int)ceil_div(rows, 4);  // four rows per work-group
-    if (num_videos == 1) launch_finish<true>(a, bf16, d->head_dim, fgrid, s);
-    else launch_finish<false>(a, bf16, d->head_dim, fgrid, s);
+    if (a.qps > 1 && p.max_chunks <= 16) {
+        // Whole branches have many rows of few slots: batches of 8 or 16, so
+        // that no wave loads its last slot over and over (17472 rows of 4
+        // slots: 29 us with the 64-slot batch).
+        if (d->head_dim == 128) {
+            if (p.max_chunks <= 8) launch_branch_finish<128, 8>(a, fgrid, s);
+            else launch_branch_finish<128, 16>(a, fgrid, s);
+        } else {
+            if (p.max_chunks <= 8) launch_branch_finish<64, 8>(a, fgrid, s);
+            else launch_branch_finish<64, 16>(a, fgrid, s);
+        }
+    } else if (num_videos == 1) {
+        launch_finish<true>(a, bf16, d->head_dim, fgrid, s);
+    } else {
+        launch_finish<false>(a, bf16, d->head_dim, fgrid, s);
+    }
     return launch_status();
 }
 

@@ -91,8 +91,10 @@ struct StepArgs {
     int slot0;
 };
 
-// Launch of the matrix-core split pass (its own translation unit).
+// Launches of the matrix-core split passes (their own translation unit): the
+// decode step's, and whole branches'.
 void launch_split_mfma(const StepArgs& a, int shape, int grid, hipStream_t stream);
+void launch_branch(const StepArgs& a, int own_bound, bool rows_first, hipStream_t stream);
 
 struct VideoInfo {
     int p0, L, e0, E;

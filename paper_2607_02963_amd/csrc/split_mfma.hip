@@ -9,15 +9,16 @@
 
 #include "kernel_mfma.h"
 #include "kernel_mfma32.h"
+#include "kernel_branch.h"
 
 namespace pdec {
 
 namespace {
 
-template <int D, bool PLAN, bool MQ>
+template <int D, bool PLAN>
 void launch_shape(const StepArgs& a, int shape, int grid, hipStream_t s)
 {
-    if constexpr (D == 128 && !MQ) {
+    if constexpr (D == 128) {
         // 32-row tiles (decode step at D = 128): 256 rows as eight row waves,
         // 128 rows as four row waves x two key groups
         if (shape == 4) {
@@ -30,48 +31,58 @@ void launch_shape(const StepArgs& a, int shape, int grid, hipStream_t s)
         }
     }
     switch (shape) {
-    case 1: hipLaunchKernelGGL((split_mfma_kernel<D, 1, 4, 2, PLAN, MQ>), dim3(grid), dim3(512), 0, s, a); break;
+    case 1: hipLaunchKernelGGL((split_mfma_kernel<D, 1, 4, 2, PLAN>), dim3(grid), dim3(512), 0, s, a); break;
     case 2:
-        // 128 rows: eight one-tile row waves x two key groups for the decode
-        // step at D = 128 (3-4% faster than four two-tile row waves on the
-        // decode loop and the ragged batch); four two-tile row waves
-        // otherwise (whole branches, D = 64, and the self-only plan mask,
-        // whose sixteen-wave form the compiler gives private memory)
-        if constexpr (D == 128 && !MQ && !PLAN)
-            hipLaunchKernelGGL((split_mfma_kernel<D, 1, 8, 2, PLAN, MQ>), dim3(grid), dim3(1024), 0, s, a);
+        // 128 rows: eight one-tile row waves x two key groups at D = 128
+        // (3-4% faster than four two-tile row waves on the decode loop and
+        // the ragged batch); four two-tile row waves otherwise (D = 64, and
+        // the self-only plan mask, whose sixteen-wave form the compiler gives
+        // private memory)
+        if constexpr (D == 128 && !PLAN)
+            hipLaunchKernelGGL((split_mfma_kernel<D, 1, 8, 2, PLAN>), dim3(grid), dim3(1024), 0, s, a);
         else
-            hipLaunchKernelGGL((split_mfma_kernel<D, 2, 4, 2, PLAN, MQ>), dim3(grid), dim3(512), 0, s, a);
+            hipLaunchKernelGGL((split_mfma_kernel<D, 2, 4, 2, PLAN>), dim3(grid), dim3(512), 0, s, a);
         break;
     default:
-        // 256 rows: sixteen one-tile row waves for the decode step at D = 128
-        // (four waves per SIMD hide more latency than eight two-tile waves);
-        // eight two-tile waves for whole branches, whose masked blocks run
-        // faster that way, and at D = 64, whose sixteen-wave form the
-        // compiler gives private-memory arrays
-        if constexpr (D == 128 && !MQ)
-            hipLaunchKernelGGL((split_mfma_kernel<D, 1, 16, 1, PLAN, MQ>), dim3(grid), dim3(1024), 0, s, a);
+        // 256 rows: sixteen one-tile row waves at D = 128 (four waves per SIMD
+        // hide more latency than eight two-tile waves); eight two-tile waves
+        // at D = 64, whose sixteen-wave form the compiler gives private-memory
+        // arrays
+        if constexpr (D == 128)
+            hipLaunchKernelGGL((split_mfma_kernel<D, 1, 16, 1, PLAN>), dim3(grid), dim3(1024), 0, s, a);
         else
-            hipLaunchKernelGGL((split_mfma_kernel<D, 2, 8, 1, PLAN, MQ>), dim3(grid), dim3(512), 0, s, a);
+            hipLaunchKernelGGL((split_mfma_kernel<D, 2, 8, 1, PLAN>), dim3(grid), dim3(512), 0, s, a);
         break;
     }
 }
 
 }  // namespace
 
-// The self-only plan mask and whole branches (several queries per stream)
-// have kernels of their own, so that the decode step's inner loop carries
-// none of their tests.  The two are not combined (the host refuses it).
+// The self-only plan mask has kernels of its own, so that the full design's
+// inner loop carries none of its tests.
 void launch_split_mfma(const StepArgs& a, int shape, int grid, hipStream_t stream)
 {
-    const bool plan = a.plan_T > 0, mq = a.qps > 1;
+    const bool plan = a.plan_T > 0;
     if (a.D == 128) {
-        if (mq) launch_shape<128, false, true>(a, shape, grid, stream);
-        else if (plan) launch_shape<128, true, false>(a, shape, grid, stream);
-        else launch_shape<128, false, false>(a, shape, grid, stream);
+        if (plan) launch_shape<128, true>(a, shape, grid, stream);
+        else launch_shape<128, false>(a, shape, grid, stream);
     } else {
-        if (mq) launch_shape<64, false, true>(a, shape, grid, stream);
-        else if (plan) launch_shape<64, true, false>(a, shape, grid, stream);
-        else launch_shape<64, false, false>(a, shape, grid, stream);
+        if (plan) launch_shape<64, true>(a, shape, grid, stream);
+        else launch_shape<64, false>(a, shape, grid, stream);
+    }
+}
+
+// Whole branches: 64 rows per wave (two tiles), 32 where a video has at most
+// 128 rows per kv head and half of the waves would idle.
+void launch_branch(const StepArgs& a, int own_bound, bool rows_first, hipStream_t s)
+{
+    const dim3 grid((unsigned)(8 * ((a.n_items + 7) / 8))), block(256);
+    if (a.D == 128) {
+        if (a.rows_per_item == 256) hipLaunchKernelGGL((branch_kernel<128, 2, 4>), grid, block, 0, s, a, own_bound, (int)rows_first);
+        else hipLaunchKernelGGL((branch_kernel<128, 1, 4>), grid, block, 0, s, a, own_bound, (int)rows_first);
+    } else {
+        if (a.rows_per_item == 256) hipLaunchKernelGGL((branch_kernel<64, 2, 4>), grid, block, 0, s, a, own_bound, (int)rows_first);
+        else hipLaunchKernelGGL((branch_kernel<64, 1, 4>), grid, block, 0, s, a, own_bound, (int)rows_first);
     }
 }
 

@@ -333,3 +333,18 @@ def test_long_single_head_prefix_plans_more_slots_than_one_finish_batch():
     f32 = pdec.describe_plan(pdec.make_dims(3, 8, 1, 128, 40, 20000, pdec.PDEC_DTYPE_F32))
     assert bf["merge_pass"] == 1 and bf["max_chunks"] > 128
     assert f32["merge_pass"] == 1 and f32["max_chunks"] > 64
+
+
+@pytest.mark.parametrize("E,N,L,H_q,H_kv,D", [(13, 48, 32768, 28, 4, 128), (1, 2, 40000, 1, 1, 64),
+                                               (24, 80, 16000, 40, 8, 128), (1, 16384, 0, 28, 4, 128)])
+def test_whole_branch_plan_stays_within_the_static_scratch_unless_it_has_one_slot(E, N, L, H_q, H_kv, D):
+    """More chunks are planned only while their states fit the buffer of
+    pdec_attn_step_noalloc, so no call outgrows it by being cut finer."""
+    d = pdec.make_dims(E, H_q, H_kv, D, N, L, pdec.PDEC_DTYPE_BF16, queries_per_stream=N)
+    info = pdec.describe_plan(d)
+    assert info["max_chunks"] == 1 or pdec.workspace_size(d) <= 32 << 20
+    assert info["merge_pass"] == int(info["max_chunks"] > 1)
+    assert info["work_items"] == info["max_chunks"] * info["row_groups"] * H_kv
+    assert info["row_groups"] == -(-E * N * (H_q // H_kv) // info["rows_per_item"])
+    units = -(-L // 64) + (1 if E > 1 else -(-N // 64))
+    assert info["max_chunks"] * info["chunk_keys"] >= 64 * units

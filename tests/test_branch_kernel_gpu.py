@@ -1,0 +1,67 @@
+"""The whole-branch kernel (queries_per_stream > 1) at the edges of its tiles,
+row groups, chunks and masks, against the oracle's attn_prefill.
+
+Rows of a kv head come in waves of 32 or 64 and groups of 128 or 256; keys in
+64-key units, two 32-key blocks each; a long prefix is cut into chunks merged
+by the finish pass in batches of 8, 16 or 64 slots.  The bar is the bf16 one
+(P and the result are rounded to bf16): max-abs 2e-2, normwise 1e-2.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import check, dev_float, dev_int, host
+from paper_2607_02963_amd import pdec
+from paper_2607_02963_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # E, N, L, lens, H_q, H_kv, D, cap, cross
+    (1, 2, 1, [2], 1, 1, 128, 2, 0),                      # two rows, one prefix key
+    (2, 64, 31, [64, 33], 1, 1, 128, 64, 0),              # 128 rows: the one-tile shape, full
+    (3, 43, 65, [43, 43, 1], 1, 1, 128, 70, 0),           # 129 rows: the two-tile shape; cache longer than the branch
+    (1, 256, 33, [200], 1, 1, 64, 256, 0),                # one group, every unit of one stream; rows past the cache
+    (1, 257, 64, [257], 1, 1, 128, 300, 0),               # one row in the second group
+    (5, 13, 1983, [13, 0, 7, 13, 1], 14, 2, 128, 16, 0),  # several chunks, a partial last prefix unit
+    (9, 40, 130, [40, 64, 3, 40, 0, 40, 39, 33, 32], 4, 1, 128, 64, 1),  # other streams' units, lengths above N
+    (70, 2, 200, [2] * 69 + [0], 2, 2, 64, 2, 1),         # more streams than one scan of the unit table
+    (40, 8, 6000, [8] * 40, 28, 4, 128, 8, 0),            # few-slot rows
+    (2, 3, 9000, [3, 3], 2, 1, 128, 3, 0),                # many slots per row
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[f"E{c[0]}N{c[1]}L{c[2]}d{c[6]}x{c[8]}" for c in CASES])
+def test_branch_edges_match_oracle(case):
+    E, N, L, lens, H_q, H_kv, D, cap, cross = case
+    rng = np.random.default_rng(100 + E + N + L)
+    f = lambda s, *shape: wl.bf16_bits((s * rng.standard_normal(shape)).astype(np.float32))  # noqa: E731
+    # scores of about 1.5 nats, values that the output bar can tell apart
+    q, kp, vp = f(1.5, E, N, H_q, D), f(1.0, L, H_kv, D), f(0.5, L, H_kv, D)
+    ke, ve = f(1.0, E, cap, H_kv, D), f(0.5, E, cap, H_kv, D)
+    n = np.asarray(lens, np.int32)
+    out, lse = pdec.attn_prefill(dev_float(q, "bf16"), dev_float(kp, "bf16"), dev_float(vp, "bf16"),
+                                 dev_float(ke, "bf16"), dev_float(ve, "bf16"), dev_int(n), dev_int([L]), cross=cross)
+    torch.cuda.synchronize()
+    ref_o, ref_l = oracle.attn_prefill(q, kp, vp, ke, ve, n, [0, L], [0, E], cross=cross)
+    check("bf16", host(out).reshape(E * N, H_q, D), host(lse).reshape(E * N, H_q), ref_o.reshape(E * N, H_q, D),
+          ref_l.reshape(E * N, H_q), what=f"branch edges {case}")
+
+
+def test_branch_prefix_shorter_than_its_bound():
+    """The plan's chunks follow the bound on the prefix; the video's prefix,
+    in device memory, may be shorter, leaving slots that hold no state."""
+    rng = np.random.default_rng(5)
+    E, N, L, room, H_q, H_kv, D = 3, 20, 777, 5000, 14, 2, 128
+    f = lambda *shape: wl.bf16_bits(rng.standard_normal(shape).astype(np.float32))  # noqa: E731
+    q, kp, vp, ke, ve = f(E, N, H_q, D), f(room, H_kv, D), f(room, H_kv, D), f(E, N, H_kv, D), f(E, N, H_kv, D)
+    n = np.array([20, 5, 20], np.int32)
+    dims = pdec.make_dims(E, H_q, H_kv, D, N, room, pdec.PDEC_DTYPE_BF16, queries_per_stream=N)
+    ws = torch.full((pdec.workspace_size(dims),), 255, dtype=torch.uint8, device="cuda")  # NaN patterns
+    out, lse = pdec.attn_prefill(dev_float(q, "bf16"), dev_float(kp, "bf16"), dev_float(vp, "bf16"),
+                                 dev_float(ke, "bf16"), dev_float(ve, "bf16"), dev_int(n), dev_int([L]), workspace=ws)
+    torch.cuda.synchronize()
+    ref_o, ref_l = oracle.attn_prefill(q, kp[:L], vp[:L], ke, ve, n, [0, L], [0, E])
+    check("bf16", host(out).reshape(E * N, H_q, D), host(lse).reshape(E * N, H_q), ref_o.reshape(E * N, H_q, D),
+          ref_l.reshape(E * N, H_q), what="branch short prefix")
