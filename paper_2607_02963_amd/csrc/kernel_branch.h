@@ -70,11 +70,14 @@ __device__ inline int branch_vswz(int key)
 // offsets into LDS, M0 left changed (dma_16B_sbase restores it; a reserved
 // register, which the compiler sets right before each instruction of its own
 // that reads it).
-__device__ inline void dma_16B_m0(const void* base, uint32_t off, uint32_t lds_base)
+// lanes is the set of lanes that load, all or none: a piece without lanes
+// moves nothing but counts as one on the wave's counter.  Called with every
+// lane of the wave active.
+__device__ inline void dma_16B_m0(const void* base, uint32_t off, uint32_t lds_base, uint64_t lanes)
 {
     const uint64_t sb = sgpr_base(base);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :
-                 : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(off), "s"(sb)
+    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b64 exec, -1" :
+                 : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(off), "s"(sb), "s"(sgpr_base(reinterpret_cast<const void*>(lanes)))
                  : "memory");
 }
 
@@ -186,7 +189,7 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
     const int u0 = c_idx * upc;
     // the last slot takes whatever is left
     const int u1 = c_idx == nch - 1 ? upre + own : min(u0 + upc, upre + own);
-    const int nst = max(0, u1 - u0);
+    const int nst = __builtin_amdgcn_readfirstlane(max(0, u1 - u0));
     // stages of the pipelined loop: all of them where every own unit belongs
     // to the rows' one stream, else the prefix's (own units then concern few
     // waves each, which the plain loop skips)
@@ -228,18 +231,18 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
         choff[i] = 16u * ((lane % C::CH) ^ (w_is_v ? branch_vswz<D>(key) : branch_kswz<D>(key)));
     }
     const uint32_t m_base = lds_u32(lds) + (w_is_v ? C::STAGE_K : 0) + pk0 * 1024;
-    // Stages past the last re-read the last one (into a slot that is not read
-    // again), so that every wait below counts the same pieces.
-    struct Pending { const uint16_t* base; uint32_t dst; int nk; };
+    // Stages past the last are pieces without lanes, so that every wait below
+    // counts the same pieces.
+    struct Pending { const uint16_t* base; uint32_t dst; int nk; uint64_t lanes; };
     auto pending = [&](int st) __attribute__((always_inline)) {
         const UnitInfo ui = unit(u0 + min(st, nst - 1));
         return Pending{reinterpret_cast<const uint16_t*>(pre + (ui.stream < 0 ? 0 : evt_pre) + 2 * ui.key_off),
-                       m_base + (st % C::NSTAGE) * C::STAGE, ui.nk};
+                       m_base + (st % C::NSTAGE) * C::STAGE, ui.nk, st < nst ? ~0ull : 0ull};
     };
     auto issue_piece = [&](const Pending& pd, int i) __attribute__((always_inline)) {
         // keys past the last valid one re-read it (their scores are masked)
         const uint32_t row = key0 < pd.nk - i * C::KPI ? k0off + i * C::KPI * strideB : (uint32_t)(pd.nk - 1) * strideB;
-        dma_16B_m0(pd.base, row + choff[i & 3], pd.dst + 1024 * i);
+        dma_16B_m0(pd.base, row + choff[i & 3], pd.dst + 1024 * i, pd.lanes);
     };
     auto issue_stage = [&](const Pending& pd) __attribute__((always_inline)) {
 #pragma unroll

@@ -161,58 +161,62 @@ void size_workspace(const pdec_dims* d, int num_videos, Plan* p)
     p->ws_bytes = p->part_o_bytes + p->part_ml_bytes + (size_t)num_videos * sizeof(int32_t);
 }
 
-// Whole branches (kernel_branch.h).  A row group of 256 rows (128 when a
-// video has no more) sees the prefix units and the own units of the streams
-// its rows belong to; the chunk count is the one with the least estimated
-// time: the rounds its items take on the compute units, each an item's units
-// plus a fixed cost, and the finish pass over the slots.
+// Whole branches (kernel_branch.h).  A row group sees the prefix units and the
+// own units of the streams its rows belong to.  Row group (256 or 128 rows)
+// and chunk count are the pair with the least estimated time: the rounds its
+// items take on the compute units, each an item's units plus a fixed cost, and
+// the finish pass over the slots.  A unit takes about 2.1 us at 256 rows (the
+// 16384-token causal prefill) and a little over half of that at 128, whose
+// waves read the LDS twice as often per row: 256 rows serve the long cases,
+// 128 those with too few items to fill the chip.
 Plan make_branch_plan(const pdec_dims* d, int num_videos)
 {
-    Plan p{};
     const int G = d->num_q_heads / d->num_kv_heads;
     const int ev = events_per_video(d);
     const long N = d->queries_per_stream;
     const long per = N * G, rows_max = ev * per;
-    p.path = kPathMfma;
-    p.rows_per_item = rows_max > 128 ? 256 : 128;
-    p.shape = rows_max > 128 ? 7 : 6;
-    p.rg_max = (int)ceil_div(rows_max, p.rows_per_item);
-    // own units of one row group: every stream but the last it touches may be
-    // seen whole, the last up to the group's tokens of it
+    const long upre = ceil_div(d->max_prefix_len, kUnitKeys);
     const long full = ceil_div(std::min<long>(d->event_cap, N), kUnitKeys);
-    long own = full * ev;
-    if (!d->cross_causal) {
-        const long spans = std::min<long>(ev, (p.rows_per_item - 2) / per + 2);
-        const long last = std::min(full, ceil_div(p.rows_per_item / G + 2, kUnitKeys));
-        if (spans >= 2) own = (spans - 1) * full + last;
-        else own = full;
-    }
-    const long upre = ceil_div(d->max_prefix_len, kUnitKeys), units = std::max<long>(upre + own, 1);
-    p.own_bound = (int)std::min<long>(own, 1L << 24);
-    p.rows_first = num_videos > 1 || own > upre;
     const long tokens = d->prefix_tokens > 0 ? d->prefix_tokens : (long)num_videos * d->max_prefix_len;
-    const double rows = (double)d->num_events * d->num_q_heads * N;
-    // a stream's rows see half of its units on average
-    const double mean_units = (double)tokens / num_videos / kUnitKeys + (d->cross_causal ? own : 0.5 * own);
-    const double unit_us = p.rows_per_item == 256 ? 1.4 : 0.9, fixed_units = 4.0;
-    double best = 0.0;
-    long chunks = 1;
-    for (long n = 1; n <= std::min<long>(units, kMaxChunks); ++n) {
-        if (n > 1 && n * rows * (d->head_dim * 2 + 8) + num_videos * 4.0 > (double)PDEC_NOALLOC_SCRATCH_BYTES) break;
-        const long upc = ceil_div(units, n);
-        if (ceil_div(units, upc) != n) continue;  // fewer chunks of the same length do
-        const double items = (double)num_videos * d->num_kv_heads * p.rg_max * n;
-        double t = p.rows_first ? std::max(upc + fixed_units, items * (mean_units / n + fixed_units) / kTargetItems)
-                                : std::ceil(items / kTargetItems) * (upc + fixed_units);
-        t *= unit_us;
-        if (n > 1) t += 4.0 + rows * n * (d->head_dim * 2 + 8) / 4.0e6;
-        if (n == 1 || t < best) {
+    const double rows = (double)d->num_events * d->num_q_heads * N, slot_bytes = d->head_dim * 2 + 8;
+    double best = -1.0;
+    Plan p{};
+    for (const int rt : {256, 128}) {
+        const long rg = ceil_div(rows_max, rt);
+        // own units of one row group: every stream but the last it touches may
+        // be seen whole, the last up to the group's tokens of it
+        long own = full * ev;
+        if (!d->cross_causal) {
+            const long spans = std::min<long>(ev, (rt - 2) / per + 2);
+            own = spans >= 2 ? (spans - 1) * full + std::min(full, ceil_div(rt / G + 2, kUnitKeys)) : full;
+        }
+        const long units = std::max<long>(upre + own, 1);
+        const bool rows_first = num_videos > 1 || own > upre;
+        // a stream's rows see half of its units on average
+        const double mean_units = (double)tokens / num_videos / kUnitKeys + (d->cross_causal ? own : 0.5 * own);
+        const double unit_us = rt == 256 ? 2.1 : 1.3, fixed_units = 4.0;
+        for (long n = 1; n <= std::min<long>(units, kMaxChunks); ++n) {
+            // no more states than the scratch of pdec_attn_step_noalloc holds
+            if (n > 1 && n * rows * slot_bytes + num_videos * 4.0 > (double)PDEC_NOALLOC_SCRATCH_BYTES) break;
+            const long upc = ceil_div(units, n);
+            if (ceil_div(units, upc) != n) continue;  // fewer chunks of the same length do
+            const double items = (double)num_videos * d->num_kv_heads * rg * n;
+            double t = rows_first ? std::max(upc + fixed_units, items * (mean_units / n + fixed_units) / kTargetItems)
+                                  : std::ceil(items / kTargetItems) * (upc + fixed_units);
+            t *= unit_us;
+            if (n > 1) t += 4.0 + rows * n * slot_bytes / 4.0e6;
+            if (best >= 0.0 && t >= best) continue;
             best = t;
-            chunks = n;
+            p.rows_per_item = rt;
+            p.rg_max = (int)rg;
+            p.own_bound = (int)std::min<long>(own, 1L << 24);
+            p.rows_first = rows_first;
+            p.unit_per_chunk = (int)std::min<long>(upc, 1L << 24);
+            p.max_chunks = (int)n;
         }
     }
-    p.unit_per_chunk = (int)std::min<long>(ceil_div(units, chunks), 1L << 24);
-    p.max_chunks = (int)ceil_div(units, p.unit_per_chunk);
+    p.path = kPathMfma;
+    p.shape = p.rows_per_item == 256 ? 7 : 6;
     p.n_items = (long)num_videos * d->num_kv_heads * p.max_chunks * p.rg_max;
     size_workspace(d, num_videos, &p);
     return p;

@@ -72,8 +72,8 @@ void launch_split_mfma(const StepArgs& a, int shape, int grid, hipStream_t strea
     }
 }
 
-// Whole branches: 64 rows per wave (two tiles), 32 where a video has at most
-// 128 rows per kv head and half of the waves would idle.
+// Whole branches: 64 rows per wave (two tiles) in groups of 256 rows, 32 in
+// groups of 128.
 void launch_branch(const StepArgs& a, int own_bound, bool rows_first, hipStream_t s)
 {
     const dim3 grid((unsigned)(8 * ((a.n_items + 7) / 8))), block(256);
