@@ -493,10 +493,11 @@ size_t pdec_backward_workspace_size(const pdec_dims* dims);
  *   lse [E, N, H_q]               device, float32, the forward's lse;
  *   dq [E, N, H_q, D], dk_prefix, dv_prefix [Lmax, H_kv, D],
  *   dk_event, dv_event [E, cap, H_kv, D]
- *                                 device, float32, 16-byte aligned, every element written;
+ *                                 device, float32, 16-byte aligned, every element written
+ *                                 (they may hold partial sums while the call runs);
  *   workspace >= pdec_backward_workspace_size(dims) bytes, device.
  * Prefix pointers may be NULL when max_prefix_len is 0.  Asynchronous on
- * `stream` (three launches).  Returns a pdec_status.
+ * `stream` (two to four launches).  Returns a pdec_status.
  */
 int pdec_attn_prefill_backward(const pdec_dims* dims, const void* q, const void* k_prefix, const void* v_prefix,
                                const void* k_event, const void* v_event, const int32_t* event_lens,

@@ -9,33 +9,36 @@
 //   dq_i = tau sum_k ds_ik k_k,  dk_k = tau sum_i ds_ik q_i,  dv_k = sum_i p_ik dO_i.
 // Rows of ended streams (n_e <= 0) have no output and add nothing.
 //
-// Three kernels, all on v_mfma_f32_16x16x32_bf16 for the scores and
-// v_mfma_f32_16x16x16_bf16 for the products that run over 16 query rows or
-// 16 keys:
-//  1. D_i for every row (16 lanes per row);
-//  2. dk, dv: one work-group per 64-key unit (a prefix unit, or 64 rows of
-//     one stream's cache) and kv head; wave w holds keys 16w .. 16w + 15 as
-//     the B operands of S = Q K^T and dP = dO V^T, and loops over 64-row
-//     tiles of the rows that can see the unit, staged through LDS (four
-//     16-row sub-tiles between barriers).  The S
-//     accumulator gives a lane key l % 16 for rows 4(l/16) .. +3, which is the
-//     A operand (keys x rows) of dV += P^T dO and dK += dS^T Q; their B
-//     operands (rows x d) come from the row tiles with the transposing LDS
-//     read.  Every key of the unit is written once (0 where no row sees it);
-//  3. dq: one work-group per 64 rows and kv head (eight waves: each 16-row
-//     block is held by two waves that split each key tile); a wave holds its
-//     16 rows as the B operands of S^T = K Q^T and dP^T = V dO^T, and
-//     loops over 128-key tiles (prefix, then the own rows of its rows'
-//     streams) staged through LDS.  The S^T accumulator gives a lane row
-//     l % 16 for keys 4(l/16) .. +3, the A operand (rows x keys) of
-//     dQ += dS K, whose B operand (keys x d) is the transposing read of the
-//     key tile.
-// Tiles are stored with the 16-byte chunks of a row permuted by the row
-// index, so the operand reads of 16 rows hit distinct banks.  P and dS meet
-// the matrix cores in bf16 (as the forward's P does); every sum is float32.
+// Passes, on v_mfma_f32_32x32x16_bf16 (1 only where 2 runs before 3, which
+// otherwise leaves D itself):
+//  1. per row: D_i, infinite for the rows of ended streams;
+//  2. dk, dv: a work-group holds 128 keys of one kv head (32 per wave, K and V
+//     as B operands in registers) and walks the rows that see them in stages
+//     of 64.  S = Q K^T and dP = dO V^T give a lane one key and 16 rows of a
+//     32-row tile, which is the A operand (keys x rows) of dV += P^T dO and
+//     dK += dS^T Q; their B operands (rows x d) are transposing LDS reads of
+//     the same stage;
+//  3. dq: a work-group holds 256 rows of one kv head (64 per wave, Q and dO as
+//     B operands in registers) and walks 64-key units, as the forward does.
+//     S^T = K Q^T and dP^T = V dO^T give a lane one row and 16 keys, the B
+//     operand of dQ^T += K^T dS^T, whose A operand is the transposing read;
+//  4. where 2 is split over rows or 3 over keys to fill the chip, the sum of
+//     the splits, in a fixed order.  Only one of the two is split: it runs
+//     first, its splits after the first in the output buffers that the other
+//     pass writes afterwards, so the workspace is the row values alone.
+// P and dS meet the matrix cores in bf16 (as the forward's P does); every sum
+// is float32.  Every output element is written, so nothing needs clearing, and
+// repeated calls agree bit for bit.
+//
+// What bounds 2 and 3 and why these tiles: dense contractions, so the matrix
+// cores should.  32 keys (or 64 rows) per wave keep the LDS reads at or below
+// the products' time, which 16 did not, and the 32x32x16 product runs at the
+// full rate where the 16x16x16 one of the earlier form ran at half.  One wave
+// per SIMD holds the operands and sums in 512 registers; the vector work of
+// one 32-row tile is issued under the products of the other.
 #pragma once
 
-#include "kernel_mfma.h"
+#include "kernel_branch.h"
 
 namespace pdec {
 
@@ -52,51 +55,88 @@ struct BwdArgs {
     const uint16_t* out;   // [E, N, H_q, D]
     const float* lse;      // [E, N, H_q]
     const uint16_t* dout;  // [E, N, H_q, D]
-    float* drow;           // [E * N * H_q]
+    float* drow;           // [E, N, H_q]: D, +inf for the rows of ended streams
     float* dq;             // [E, N, H_q, D]
     float* dkp;            // [Lmax, H_kv, D]
     float* dvp;
     float* dke;            // [E, cap, H_kv, D]
     float* dve;
+    // Splits after the first of the split pass: split k of dk, dv at part0 +
+    // (2 k - 2) and (2 k - 1) tensors; split k of dq in part0, then part1,
+    // part_n tensors in each.
+    float* part0;
+    float* part1;
+    long part_n;
+    long part_elems;       // elements of one split tensor
+    int row_splits, key_splits;
     int E, N, H_q, H_kv, G, cap, Lmax;
+    int R;                 // rows per kv head: E N G
+    int unit_per_chunk;    // 64-key units per key split
     float c;    // tau * log2(e)
     float tau;  // softmax scale
 };
 
-__device__ inline f32x4_t mfma_16x16x16(s16x4_t a, s16x4_t b, f32x4_t c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
-}
-
-__device__ inline s16x4_t pack_bf16x4(float a, float b, float c, float d)
-{
-    return __builtin_bit_cast(s16x4_t, u32x2_t{pack_bf16x2(a, b), pack_bf16x2(c, d)});
-}
-
-// Row r (0 .. E*N*G - 1) of kv head g: stream r / (N G), token (r / G) % N,
-// head g G + r % G; its index in q, out, dout, lse and drow.
+// Row r (0 .. R - 1) of kv head g: stream r / (N G), token (r / G) % N, head
+// g G + r % G; its index in q, out, dout and lse.
 __device__ inline long bwd_qrow(const BwdArgs& a, int g, int r)
 {
-    const int e = r / (a.N * a.G), j = (r / a.G) % a.N, hh = r % a.G;
-    return ((long)e * a.N + j) * a.H_q + g * a.G + hh;
+    return (long)(r / a.G) * a.H_q + g * a.G + r % a.G;
 }
 
-// Byte offset of 16-byte chunk ch of row `row` in a staged tile of D-wide bf16 rows.
-template <int D>
-__device__ inline int tile_off(int row, int ch)
+// One float per lane straight into LDS, lane l's at lds_base + 4 l; lanes as
+// for dma_16B_m0.
+__device__ inline void dma_4B_m0(const void* base, uint32_t off, uint32_t lds_base, uint64_t lanes)
 {
-    return row * (2 * D) + 16 * (ch ^ (row % (D / 8)));
+    const uint64_t sb = sgpr_base(base);
+    asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, %3\n\tglobal_load_lds_dword %1, %2\n\ts_mov_b64 exec, -1" :
+                 : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(off), "s"(sb),
+                   "s"(sgpr_base(reinterpret_cast<const void*>(lanes)))
+                 : "memory");
 }
 
-// Transposing read of a staged tile: lane l receives column 16 dt + l % 16 of
-// rows r0 + 4(l/16) .. +3, the B operand (rows x d) of a 16x16x16 product.
+// Permutation of the 16-byte chunks of staged row `row` (chunk ch sits at
+// ch ^ swizzle): a staged tile is read both by rows (16 rows of one chunk per
+// LDS phase) and transposed (four rows of four chunks), so 16 rows take 16
+// different permutations and four consecutive ones differ in the chunk's
+// upper bits.
 template <int D>
-__device__ inline s16x4_t tile_tr(const unsigned char* tile, int r0, int dt, int l16, int lg)
+__device__ inline int bwd_swz(int row)
 {
-    const int row = r0 + 4 * lg + (l16 >> 2);
-    const int ch = 2 * dt + ((l16 & 3) >> 1);
-    const unsigned char* p = tile + tile_off<D>(row, ch) + 8 * (l16 & 1);
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)p);
+    return D == 128 ? 4 * (row & 3) + ((row >> 2) & 3) : 4 * ((row >> 1) & 1) + ((row >> 2) & 3);
+}
+
+// Offsets of the operand reads of a staged 32-row tile: by rows, step t (row
+// l % 32, chunk 2 t + l / 32) at row ^ 32 t; transposed, rows 16 s + 8 r +
+// 4 (l / 32) .. +3 of d 32 dt + l % 32, at (tr[dt] ^ 32 r) + (16 s + 8 r) rows.
+template <int D>
+struct BwdOffsets {
+    int row;
+    int tr[D / 32];
+    __device__ explicit BwdOffsets(int lane)
+    {
+        row = (lane & 31) * 2 * D + 16 * ((lane >> 5) ^ bwd_swz<D>(lane & 31));
+        const int q = lane >> 4, i = lane & 15, r = 4 * (q >> 1) + (i >> 2);
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+            tr[dt] = r * 2 * D + 16 * ((4 * dt + 2 * (q & 1) + ((i & 3) >> 1)) ^ bwd_swz<D>(r)) + 8 * (i & 1);
+    }
+};
+
+template <int D>
+__device__ inline u32x4_t bwd_read_row(const unsigned char* tile, const BwdOffsets<D>& off, int t)
+{
+    return *reinterpret_cast<const u32x4_t*>(tile + (off.row ^ (32 * t)));
+}
+
+template <int D>
+__device__ inline u32x4_t bwd_read_tr(const unsigned char* tile, const BwdOffsets<D>& off, int s, int dt)
+{
+    typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+    const unsigned char* p = tile + 16 * s * 2 * D;
+    const u32x2_t x0 = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(p + off.tr[dt])));
+    const u32x2_t x1 = __builtin_bit_cast(
+        u32x2_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(p + 8 * 2 * D + (off.tr[dt] ^ 32))));
+    return u32x4_t{x0.x, x0.y, x1.x, x1.y};
 }
 
 // ---- 1: D_i = <dO_i, O_i> ----
@@ -105,331 +145,435 @@ __global__ __launch_bounds__(256) void bwd_drow_kernel(BwdArgs a)
 {
     constexpr int PER = D / 16;  // elements per lane, 16 lanes per row
     const long rows = (long)a.E * a.N * a.H_q;
-    const long i = (long)blockIdx.x * 16 + threadIdx.x / 16;
-    const int l = threadIdx.x % 16;
+    const long i = (long)wg_id() * 16 + wi_id() / 16;
+    const int l = wi_id() % 16;
+    if (i >= rows) return;
     float s = 0.f;
-    if (i < rows) {
-        const uint16_t* o = a.out + i * D + PER * l;
-        const uint16_t* d = a.dout + i * D + PER * l;
+    const uint16_t* o = a.out + i * D + PER * l;
+    const uint16_t* d = a.dout + i * D + PER * l;
 #pragma unroll
-        for (int k = 0; k < PER; ++k)
-            s = fmaf(__uint_as_float((uint32_t)o[k] << 16), __uint_as_float((uint32_t)d[k] << 16), s);
-    }
+    for (int k = 0; k < PER; ++k)
+        s = fmaf(__uint_as_float((uint32_t)o[k] << 16), __uint_as_float((uint32_t)d[k] << 16), s);
 #pragma unroll
     for (int off = 8; off > 0; off >>= 1) s += __shfl_xor(s, off);
-    if (i < rows && l == 0) a.drow[i] = s;
+    const bool live = a.event_lens[i / ((long)a.N * a.H_q)] > 0;
+    if (l == 0) a.drow[i] = live ? s : __builtin_inff();
 }
 
-// ---- 2: dk, dv per 64-key unit ----
+// ---- 2: dk, dv per 128 keys ----
 template <int D>
 __global__ __launch_bounds__(256) void bwd_dkdv_kernel(BwdArgs a)
 {
-    constexpr int KS = D / 32;  // 32-wide d steps
-    constexpr int DT = D / 16;  // 16-wide d blocks
-    constexpr int CH = D / 8;   // 16-byte chunks per row
-    constexpr int TR = 64;      // rows per staged tile: four 16-row sub-tiles between barriers
-    constexpr int SPT = TR * CH / 256;  // staged chunks per thread (q and dO each)
-    __shared__ __attribute__((aligned(16))) unsigned char qs[TR * 2 * D];
-    __shared__ __attribute__((aligned(16))) unsigned char dos[TR * 2 * D];
-    __shared__ float lse2_s[TR], drow_s[TR];
-    __shared__ int tok_s[TR];
+    constexpr int ROWB = 2 * D, CH = D / 8, KS = D / 16, DT = D / 32;
+    constexpr int NSTAGE = 4, TILE = 64 * ROWB, STAGE = 2 * TILE;  // Q rows, then dO rows
+    constexpr int KPI = 1024 / ROWB, PPW = STAGE / 1024 / 4;       // rows per piece, pieces per wave
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[NSTAGE * STAGE];
+    __shared__ __attribute__((aligned(16))) float rowv[NSTAGE][2][64];  // l2, D
 
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
-    const int g = blockIdx.y;
-    const int UP = (a.Lmax + 63) / 64, UPS = (a.cap + 63) / 64;
-    const int u = blockIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(wi_id() >> 6);
+    const int lane = wi_id() & 63, l32 = lane & 31, hi = lane >> 5;
+    const int g = (int)__builtin_amdgcn_workgroup_id_y(), split = (int)__builtin_amdgcn_workgroup_id_z();
+    const int UP = (a.Lmax + 127) / 128, UPS = (a.cap + 127) / 128;
+    const int u = wg_id();
     const int L = min(max(a.prefix_len[0], 0), a.Lmax);
-    const int R = a.E * a.N * a.G;
+    const int NG = a.N * a.G;
 
-    // the unit: keys [k0, k0 + 64) of the prefix (own < 0) or of stream own's cache
-    int own = -1, k0, kend, nvalid, r_begin, r_end;
-    if (u < UP) {
-        k0 = 64 * u;
-        kend = min(k0 + 64, a.Lmax);
-        nvalid = max(0, min(kend, L) - k0);
-        r_begin = 0;
-        r_end = R;
-    } else {
-        own = (u - UP) / UPS;
-        k0 = 64 * ((u - UP) % UPS);
-        kend = min(k0 + 64, a.cap);
-        const int nf = a.event_lens[own];
-        nvalid = max(0, min(kend, nf) - k0);
-        // rows of stream `own` whose token reaches k0
-        r_begin = (own * a.N + min(k0, a.N)) * a.G;
-        r_end = (own + 1) * a.N * a.G;
-        if (nf <= 0) r_end = r_begin;
+    // keys [k0, kend) of the prefix or of stream own's cache, nvalid of them
+    // holding rows; query rows [r_begin, r_end) see some of them
+    const bool prefix = u < UP;
+    const int own = prefix ? 0 : (u - UP) / UPS;
+    const int k0 = 128 * (prefix ? u : (u - UP) % UPS);
+    const int kend = min(k0 + 128, prefix ? a.Lmax : a.cap);
+    const int nf = a.event_lens[own];
+    const int nvalid = max(0, min(kend, prefix ? L : nf) - k0);
+    int r_begin = prefix ? 0 : own * NG + min(k0, a.N) * a.G;
+    const int r_end = prefix ? a.R : (own + 1) * NG;
+    // the row splits cut the prefix's rows, or a pure causal sequence's
+    const bool cut = prefix || a.Lmax == 0;
+    if (!cut && split > 0) return;
+    int nst = nvalid > 0 ? (r_end - r_begin + 63) / 64 : 0;
+    if (cut && a.row_splits > 1) {
+        const int per = (nst + a.row_splits - 1) / a.row_splits;
+        r_begin += 64 * per * split;
+        nst = max(0, min(per, nst - per * split));
     }
+    nst = __builtin_amdgcn_readfirstlane(nst);
+    // a key's rows start at rmin: own row t is seen by tokens j >= t
+    const int rmin = prefix ? 0 : own * NG + (k0 + 32 * w + l32) * a.G;
 
-    // this wave's keys as B operands (zero past the valid ones)
-    const int key = k0 + 16 * w + l16;  // the lane's key
-    const bool kvalid = key - k0 < nvalid;
-    u32x4_t kB[KS], vB[KS];
-    {
-        const long base = own < 0 ? ((long)key * a.H_kv + g) * D : (((long)own * a.cap + key) * a.H_kv + g) * D;
-        const uint16_t* kr = (own < 0 ? a.kp : a.ke) + (kvalid ? base : 0);
-        const uint16_t* vr = (own < 0 ? a.vp : a.ve) + (kvalid ? base : 0);
+    // ---- DMA of one stage: waves 0, 1 Q rows, waves 2, 3 dO rows; wave 0 also lse, wave 1 D ----
+    const bool w_is_d = w >= 2;
+    const uint64_t qb = sgpr_base(a.q), db = sgpr_base(a.dout);
+    const uint64_t src = w_is_d ? db : qb;
+    const uint64_t lseb = sgpr_base(a.lse), drowb = sgpr_base(a.drow);
+    const uint64_t rvb = w == 0 ? lseb : drowb;
+    const int row0 = (w & 1) * PPW * KPI + lane / CH;
+    uint32_t choff[4];
 #pragma unroll
-        for (int t = 0; t < KS; ++t) {
-            kB[t] = kvalid ? *reinterpret_cast<const u32x4_t*>(kr + 32 * t + 8 * lg) : u32x4_t{0u, 0u, 0u, 0u};
-            vB[t] = kvalid ? *reinterpret_cast<const u32x4_t*>(vr + 32 * t + 8 * lg) : u32x4_t{0u, 0u, 0u, 0u};
-        }
-    }
-    f32x4_t dk[DT], dv[DT];
+    for (int i = 0; i < 4; ++i) choff[i] = 16u * ((lane % CH) ^ bwd_swz<D>(row0 + i * KPI));
+    const float inv_g = 1.f / (float)a.G;
+    const uint32_t lds0 = lds_u32(lds) + (w_is_d ? TILE : 0) + (w & 1) * PPW * 1024;
+    auto issue_stage = [&](int st) __attribute__((always_inline)) {
+        const uint64_t lanes = st < nst ? ~0ull : 0ull;
+        const int rb = r_begin + 64 * min(st, max(nst - 1, 0));
+        const int t0 = rb / a.G, h0 = rb - t0 * a.G;
+        const uint64_t base = src + 2 * D * ((long)t0 * a.H_q + g * a.G);
+        const uint32_t dst = lds0 + (st % NSTAGE) * STAGE;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) {
-        dk[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        dv[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
-
-    // row tiles of TR rows, staged through LDS; thread tid moves chunks
-    // tid + 256 m of the tile's TR x CH (q and dO) and, for tid < TR, the
-    // row's lse, D and token
-    auto fetch = [&](int rb, u32x4_t (&qv)[SPT], u32x4_t (&dv4)[SPT], float& l2, float& dr, int& tk) {
-#pragma unroll
-        for (int m = 0; m < SPT; ++m) {
-            const int cidx = tid + 256 * m, sr = cidx / CH, sc = cidx % CH, r = rb + sr;
-            qv[m] = dv4[m] = u32x4_t{0u, 0u, 0u, 0u};
-            if (r < r_end) {
-                const long qr = bwd_qrow(a, g, r);
-                qv[m] = *reinterpret_cast<const u32x4_t*>(a.q + qr * D + 8 * sc);
-                dv4[m] = *reinterpret_cast<const u32x4_t*>(a.dout + qr * D + 8 * sc);
-            }
+        for (int i = 0; i < PPW; ++i) {
+            // rows past the last re-read it (see row_values)
+            const int n = h0 + min(row0 + i * KPI, r_end - 1 - rb);
+            const int t = (int)(((float)n + 0.5f) * inv_g);  // n / G: n < G + 64
+            const uint32_t off = (uint32_t)(t * a.H_q + n - t * a.G) * (2 * D) + choff[i & 3];
+            dma_16B_m0(reinterpret_cast<const void*>(base), off, dst + 1024 * i, lanes);
         }
-        l2 = __builtin_inff();  // p = 0 for rows past the range or of ended streams
-        dr = 0.f;
-        tk = 0;
-        if (tid < TR) {
-            const int rr = rb + tid;
-            if (rr < r_end) {
-                const int e = rr / (a.N * a.G);
-                const long qr = bwd_qrow(a, g, rr);
-                tk = (rr / a.G) % a.N;
-                if (a.event_lens[e] > 0) {
-                    l2 = a.lse[qr] * kLog2eF;
-                    dr = a.drow[qr];
-                }
-            }
-        }
+        const int n = h0 + min(lane, r_end - 1 - rb);
+        const int t = (int)(((float)n + 0.5f) * inv_g);
+        dma_4B_m0(reinterpret_cast<const void*>(rvb + 4 * ((long)t0 * a.H_q + g * a.G)), 4 * (t * a.H_q + n - t * a.G),
+                  lds_u32(rowv[st % NSTAGE][w & 1]), w < 2 ? lanes : 0ull);
     };
 
-    u32x4_t qv[SPT], dv4[SPT];
-    float l2, dr;
-    int tk;
-    if (r_begin < r_end) fetch(r_begin, qv, dv4, l2, dr, tk);
-    for (int rb = r_begin; rb < r_end; rb += TR) {
-        __syncthreads();  // the previous tile is no longer read
-#pragma unroll
-        for (int m = 0; m < SPT; ++m) {
-            const int cidx = tid + 256 * m, sr = cidx / CH, sc = cidx % CH;
-            *reinterpret_cast<u32x4_t*>(qs + tile_off<D>(sr, sc)) = qv[m];
-            *reinterpret_cast<u32x4_t*>(dos + tile_off<D>(sr, sc)) = dv4[m];
-        }
-        if (tid < TR) {
-            lse2_s[tid] = l2;
-            drow_s[tid] = dr;
-            tok_s[tid] = tk;
-        }
-        __syncthreads();
-        if (rb + TR < r_end) fetch(rb + TR, qv, dv4, l2, dr, tk);  // next tile, in flight meanwhile
-        const int nsub = min(TR, r_end - rb + 15) / 16;  // 16-row sub-tiles holding rows of the range
+    // The row values of a landed stage made ready, by wave 0, one barrier
+    // before they are read: lse in base 2, infinite (so that p = 0) for rows
+    // of ended streams and rows past the last, whose D becomes 0.
+    auto row_values = [&](int st) __attribute__((always_inline)) {
+        float* const v = rowv[st % NSTAGE][0] + lane;
+        const float l = v[0], dr = v[64];
+        const bool none = dr == __builtin_inff() || r_begin + 64 * st + lane >= r_end;
+        v[0] = none ? __builtin_inff() : l * kLog2eF;
+        v[64] = none ? 0.f : dr;
+    };
 
-        for (int sub = 0; sub < nsub; ++sub) {
-            const int r0 = 16 * sub;
-            // S = Q K^T and dP = dO V^T: lane holds rows r0 + 4 lg + i of key l16
-            f32x4_t sc4 = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
+    // this wave's keys as B operands
+    u32x4_t kB[KS], vB[KS];
+    {
+        const int key = min(k0 + 32 * w + l32, max(k0 + nvalid - 1, 0));  // keys past the last repeat it; not stored
+        const long base = ((prefix ? (long)key : (long)own * a.cap + key) * a.H_kv + g) * D + 8 * hi;
+        const uint64_t kb = prefix ? sgpr_base(a.kp) : sgpr_base(a.ke), vb = prefix ? sgpr_base(a.vp) : sgpr_base(a.ve);
 #pragma unroll
-            for (int t = 0; t < KS; ++t) {
-                const u32x4_t qa = *reinterpret_cast<const u32x4_t*>(qs + tile_off<D>(r0 + l16, 4 * t + lg));
-                const u32x4_t da = *reinterpret_cast<const u32x4_t*>(dos + tile_off<D>(r0 + l16, 4 * t + lg));
-                sc4 = mfma_16x16x32(as_bf16x8(qa), as_bf16x8(kB[t]), sc4);
-                dp = mfma_16x16x32(as_bf16x8(da), as_bf16x8(vB[t]), dp);
-            }
-            float p[4], ds[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int rr = r0 + 4 * lg + i;
-                bool vis = kvalid;
-                if (own >= 0) vis = vis & (key <= tok_s[rr]);  // own row t seen by tokens j >= t
-                p[i] = vis ? fast_exp2(fmaf(sc4[i], a.c, -lse2_s[rr])) : 0.f;
-                ds[i] = p[i] * (dp[i] - drow_s[rr]);
-            }
-            const s16x4_t pa = pack_bf16x4(p[0], p[1], p[2], p[3]);
-            const s16x4_t dsa = pack_bf16x4(ds[0], ds[1], ds[2], ds[3]);
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                dv[dt] = mfma_16x16x16(pa, tile_tr<D>(dos, r0, dt, l16, lg), dv[dt]);
-                dk[dt] = mfma_16x16x16(dsa, tile_tr<D>(qs, r0, dt, l16, lg), dk[dt]);
+        for (int t = 0; t < KS; ++t) {
+            kB[t] = vB[t] = u32x4_t{0u, 0u, 0u, 0u};
+            if (nvalid > 0) {
+                kB[t] = *reinterpret_cast<const u32x4_t*>(kb + 2 * (base + 16 * t));
+                vB[t] = *reinterpret_cast<const u32x4_t*>(vb + 2 * (base + 16 * t));
             }
         }
     }
-
-    // lane holds keys 16 w + 4 lg + i, d = 16 dt + l16; every key of the unit is written
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int kk = k0 + 16 * w + 4 * lg + i;
-        if (kk >= kend) continue;
-        const long base = own < 0 ? ((long)kk * a.H_kv + g) * D : (((long)own * a.cap + kk) * a.H_kv + g) * D;
-        float* dkr = (own < 0 ? a.dkp : a.dke) + base;
-        float* dvr = (own < 0 ? a.dvp : a.dve) + base;
+    for (int st = 0; st < NSTAGE - 1; ++st) issue_stage(st);
+    wait_vmcnt<0>();  // plain loads and DMA complete in no order relative to each other
+#pragma unroll
+    for (int t = 0; t < KS; ++t) asm volatile("" : "+a"(kB[t]), "+a"(vB[t]));
+    bf32x16_t dk[DT], dv[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dk[dt][i] = dv[dt][i] = 0.f;
+    const BwdOffsets<D> off(lane);
+
+    lds_barrier();  // every wave's pieces of the first stages have landed
+    if (w == 0 && nst > 0) row_values(0);
+    for (int st = 0; st < nst; ++st) {
+        // stage st + 1 has landed too
+        stage_barrier<PPW + 1>();
+        issue_stage(st + 3);
+        if (w == 0 && st + 1 < nst) row_values(st + 1);
+        const unsigned char* qt = lds + (st % NSTAGE) * STAGE;
+        const unsigned char* dt_ = qt + TILE;
+        const int lo0 = rmin - (r_begin + 64 * st) - 4 * hi;
+        bf32x16_t s[2], dp[2];
+        u32x4_t p[2][2], ds[2][2];
+        auto scores = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s[b][i] = dp[b][i] = 0.f;
+#pragma unroll
+            for (int t = 0; t < KS; ++t) {
+                s[b] = branch_mfma(bwd_read_row<D>(qt + 32 * b * ROWB, off, t), kB[t], s[b]);
+                dp[b] = branch_mfma(bwd_read_row<D>(dt_ + 32 * b * ROWB, off, t), vB[t], dp[b]);
+            }
+        };
+        auto soft = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const f32x4_t l2 = *reinterpret_cast<const f32x4_t*>(&rowv[st % NSTAGE][0][32 * b + 8 * k + 4 * hi]);
+                const f32x4_t dr = *reinterpret_cast<const f32x4_t*>(&rowv[st % NSTAGE][1][32 * b + 8 * k + 4 * hi]);
+                float pe[4], de[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float x = fmaf(s[b][4 * k + j], a.c, -l2[j]);
+                    pe[j] = fast_exp2(32 * b + 8 * k + j >= lo0 ? x : kNegInf);
+                    de[j] = pe[j] * (dp[b][4 * k + j] - dr[j]);
+                }
+                p[b][k >> 1][2 * (k & 1)] = pack_bf16x2(pe[0], pe[1]);
+                p[b][k >> 1][2 * (k & 1) + 1] = pack_bf16x2(pe[2], pe[3]);
+                ds[b][k >> 1][2 * (k & 1)] = pack_bf16x2(de[0], de[1]);
+                ds[b][k >> 1][2 * (k & 1) + 1] = pack_bf16x2(de[2], de[3]);
+                if (k & 1) asm volatile("" : "+v"(p[b][k >> 1]), "+v"(ds[b][k >> 1]));  // computed in this phase
+            }
+        };
+        auto grads = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) {
+                    dv[dt] = branch_mfma(p[b][q], bwd_read_tr<D>(dt_ + 32 * b * ROWB, off, q, dt), dv[dt]);
+                    dk[dt] = branch_mfma(ds[b][q], bwd_read_tr<D>(qt + 32 * b * ROWB, off, q, dt), dk[dt]);
+                }
+        };
+        scores(0);
+        __builtin_amdgcn_sched_barrier(0);
+        scores(1);
+        soft(0);
+        __builtin_amdgcn_sched_barrier(0);
+        grads(0);
+        soft(1);
+        __builtin_amdgcn_sched_barrier(0);
+        grads(1);
+    }
+    wait_vmcnt<0>();  // no DMA into the LDS outlives the work-group
+
+    // lane: d 32 dt + l % 32 of keys 32 w + 8 (i / 4) + 4 (l / 32) + i % 4; every key of the tile is written
+    const bool later = cut && split > 0;
+    float* const dkb = later ? a.part0 + (2 * split - 2) * a.part_elems : prefix ? a.dkp : a.dke;
+    float* const dvb = later ? a.part0 + (2 * split - 1) * a.part_elems : prefix ? a.dvp : a.dve;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int kk = 32 * w + 8 * (i >> 2) + 4 * hi + (i & 3);
+        if (k0 + kk >= kend) continue;
+        const long base = ((prefix ? 0L : (long)own * a.cap) + k0 + kk) * a.H_kv * D + (long)g * D + l32;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
-            dkr[16 * dt + l16] = a.tau * dk[dt][i];
-            dvr[16 * dt + l16] = dv[dt][i];
+            dkb[base + 32 * dt] = kk < nvalid ? a.tau * dk[dt][i] : 0.f;
+            dvb[base + 32 * dt] = kk < nvalid ? dv[dt][i] : 0.f;
         }
     }
 }
 
-// ---- 3: dq per 64 rows ----
-// Eight waves: wave w takes rows 16 (w % 4) .. +15 of the 64 and half of the
-// 16-key blocks of each 128-key tile (the first half for w < 4); the two
-// waves of a row block add their dq through LDS at the end.
+// ---- 3: dq per 256 rows ----
 template <int D>
-__global__ __launch_bounds__(512) void bwd_dq_kernel(BwdArgs a)
+__global__ __launch_bounds__(256) void bwd_dq_kernel(BwdArgs a)
 {
-    constexpr int KS = D / 32;
-    constexpr int DT = D / 16;
-    constexpr int CH = D / 8;
-    constexpr int TK = 128;                  // keys per staged tile
-    constexpr int PER = TK * CH / 512;       // staged chunks per thread and tile (K or V)
-    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * TK * 2 * D];
-    unsigned char* ks = lds;                // K tile [TK][D]
-    unsigned char* vs = lds + TK * 2 * D;  // V tile [TK][D]
+    constexpr int ROWB = 2 * D, CH = D / 8, KS = D / 16, DT = D / 32, NT = 2;
+    constexpr int NSTAGE = 4, TILE = kUnit * ROWB, STAGE = 2 * TILE;  // K, then V
+    constexpr int KPI = 1024 / ROWB, PPW = STAGE / 1024 / 4;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[NSTAGE * STAGE];
 
-    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
-    const int w = (tid >> 6) & 3, kh = tid >> 8;  // row block, key half
-    const int g = blockIdx.y;
-    const int R = a.E * a.N * a.G;
-    const int L = min(max(a.prefix_len[0], 0), a.Lmax);
-    const int rw0 = 64 * blockIdx.x;  // first row of the work-group
-
-    // this lane's row (l16 of the wave's 16) as B operands, and its state
-    const int row = rw0 + 16 * w + l16;
-    const bool rvalid = row < R;
-    const int re = rvalid ? row / (a.N * a.G) : 0;
-    const int rtok = rvalid ? (row / a.G) % a.N : 0;
-    const bool live = rvalid && a.event_lens[re] > 0;
-    const long qr = rvalid ? bwd_qrow(a, g, row) : 0;
-    const float l2 = live ? a.lse[qr] * kLog2eF : __builtin_inff();
-    const float dr = live ? a.drow[qr] : 0.f;
-    u32x4_t qB[KS], doB[KS];
-#pragma unroll
-    for (int t = 0; t < KS; ++t) {
-        qB[t] = rvalid ? *reinterpret_cast<const u32x4_t*>(a.q + qr * D + 32 * t + 8 * lg) : u32x4_t{0u, 0u, 0u, 0u};
-        doB[t] = rvalid ? *reinterpret_cast<const u32x4_t*>(a.dout + qr * D + 32 * t + 8 * lg)
-                        : u32x4_t{0u, 0u, 0u, 0u};
-    }
-    f32x4_t acc[DT];
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) acc[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-    // key tiles: the prefix, then the cache rows of the streams of this work-group's rows
-    const int f_lo = min(rw0, R - 1) / (a.N * a.G), f_hi = min(rw0 + 63, R - 1) / (a.N * a.G);
-    const int np = (L + TK - 1) / TK;
-    int tiles = np;
-    for (int f = f_lo; f <= f_hi; ++f) tiles += (max(a.event_lens[f], 0) + TK - 1) / TK;
-    // tile t: (stream or -1, first key, valid keys)
-    auto tile_of = [&](int t, int& f, int& t0, int& nv) {
-        if (t < np) {
-            f = -1;
-            t0 = TK * t;
-            nv = min(TK, L - t0);
-            return;
-        }
-        t -= np;
-        for (f = f_lo; f <= f_hi; ++f) {
-            const int nf = max(a.event_lens[f], 0), nt = (nf + TK - 1) / TK;
-            if (t < nt) {
-                t0 = TK * t;
-                nv = min(TK, nf - t0);
-                return;
-            }
-            t -= nt;
-        }
-        f = -1;
-        t0 = 0;
-        nv = 0;  // not reached: t < tiles
+    const int w = __builtin_amdgcn_readfirstlane(wi_id() >> 6);
+    const int lane = wi_id() & 63, l32 = lane & 31, hi = lane >> 5;
+    const int g = (int)__builtin_amdgcn_workgroup_id_y(), split = (int)__builtin_amdgcn_workgroup_id_z();
+    const int NG = a.N * a.G;
+    const int row0 = 256 * wg_id(), nrows = min(256, a.R - row0);
+    const int L = min(max(a.prefix_len[0], 0), a.Lmax), upre = (L + kUnit - 1) / kUnit;
+    // the group's key sequence: the prefix units, then those of its rows'
+    // streams, each up to the group's largest token of it; one stream's
+    // units or, in turn, those of several
+    const int f_lo = row0 / NG, f_hi = (row0 + nrows - 1) / NG;
+    const int tok_last = ((row0 + nrows - 1) / a.G) % a.N;
+    auto seen = [&](int f) __attribute__((always_inline)) {
+        return min(max(a.event_lens[f], 0), f == f_hi ? tok_last + 1 : a.N);
     };
-    // staging: thread tid moves chunks tid + 512 m of the tile's TK x CH (K and V)
-    auto fetch = [&](int t, u32x4_t (&kv)[PER], u32x4_t (&vv)[PER]) {
-        int f, t0, nv;
-        tile_of(t, f, t0, nv);
-#pragma unroll
-        for (int m = 0; m < PER; ++m) {
-            const int c = tid + 512 * m, kr = c / CH, ch = c % CH;
-            kv[m] = vv[m] = u32x4_t{0u, 0u, 0u, 0u};
-            if (kr < nv) {
-                const long base = f < 0 ? ((long)(t0 + kr) * a.H_kv + g) * D
-                                        : (((long)f * a.cap + t0 + kr) * a.H_kv + g) * D;
-                kv[m] = *reinterpret_cast<const u32x4_t*>((f < 0 ? a.kp : a.ke) + base + 8 * ch);
-                vv[m] = *reinterpret_cast<const u32x4_t*>((f < 0 ? a.vp : a.ve) + base + 8 * ch);
+    int own = 0;
+    for (int f = f_lo; f <= f_hi; ++f) own += (seen(f) + kUnit - 1) / kUnit;
+    const int total = upre + own;
+    const int u0 = min(split * a.unit_per_chunk, total);
+    const int u1 = split == a.key_splits - 1 ? total : min(u0 + a.unit_per_chunk, total);
+    const int nst = __builtin_amdgcn_readfirstlane(u1 - u0);
+    // unit u, which is at or after the last one asked for through this cursor
+    struct Cursor { int f, start; };
+    auto unit = [&](Cursor& cu, int u) __attribute__((always_inline)) {
+        int stream = -1, t0 = u * kUnit, n = L;
+        if (u >= upre) {
+            int nf = seen(cu.f);
+            while (cu.f < f_hi && u - upre >= cu.start + (nf + kUnit - 1) / kUnit) {
+                cu.start += (nf + kUnit - 1) / kUnit;
+                nf = seen(++cu.f);
             }
+            stream = cu.f;
+            t0 = (u - upre - cu.start) * kUnit;
+            n = nf;
         }
+        const long row = stream < 0 ? (long)t0 : (long)stream * a.cap + t0;
+        return UnitInfo{(row * a.H_kv + g) * D, min(kUnit, n - t0), stream, t0};
+    };
+    Cursor dma_at{f_lo, 0}, at{f_lo, 0};
+
+    const bool w_is_v = w >= 2;
+    const uint64_t kpb = sgpr_base(a.kp), vpb = sgpr_base(a.vp), keb = sgpr_base(a.ke), veb = sgpr_base(a.ve);
+    const uint64_t pre = w_is_v ? vpb : kpb, evt_pre = (w_is_v ? veb : keb) - pre;
+    const uint32_t strideB = (uint32_t)a.H_kv * ROWB;
+    const int key0 = (w & 1) * PPW * KPI + lane / CH;
+    uint32_t choff[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) choff[i] = 16u * ((lane % CH) ^ bwd_swz<D>(key0 + i * KPI));
+    const uint32_t lds0 = lds_u32(lds) + (w_is_v ? TILE : 0) + (w & 1) * PPW * 1024;
+    auto issue_stage = [&](int st) __attribute__((always_inline)) {
+        const uint64_t lanes = st < nst ? ~0ull : 0ull;
+        const UnitInfo ui = unit(dma_at, u0 + min(st, nst - 1));
+        const void* base = reinterpret_cast<const void*>(pre + (ui.stream < 0 ? 0 : evt_pre) + 2 * ui.key_off);
+#pragma unroll
+        for (int i = 0; i < PPW; ++i)  // keys past the last valid one re-read it (they are masked)
+            dma_16B_m0(base, (uint32_t)min(key0 + i * KPI, ui.nk - 1) * strideB + choff[i & 3],
+                       lds0 + (st % NSTAGE) * STAGE + 1024 * i, lanes);
     };
 
-    u32x4_t kv[PER], vv[PER];
-    if (tiles > 0) fetch(0, kv, vv);
-    for (int t = 0; t < tiles; ++t) {
-        int f, t0, nv;
-        tile_of(t, f, t0, nv);
-        __syncthreads();  // the previous tile is no longer read
+    // this lane's rows: 32 nt + l % 32 of the wave's 64
+    const bool active = 64 * w < nrows;
+    int r_tok[NT], r_stream[NT];
+    float l2[NT], dr[NT];
+    u32x4_t qB[NT][KS], dB[NT][KS];
 #pragma unroll
-        for (int m = 0; m < PER; ++m) {
-            const int c = tid + 512 * m, kr = c / CH, ch = c % CH;
-            *reinterpret_cast<u32x4_t*>(ks + tile_off<D>(kr, ch)) = kv[m];
-            *reinterpret_cast<u32x4_t*>(vs + tile_off<D>(kr, ch)) = vv[m];
+    for (int nt = 0; nt < NT; ++nt) {
+        const int r = row0 + min(64 * w + 32 * nt + l32, nrows - 1);  // rows past the last repeat it; not stored
+        r_stream[nt] = r / NG;
+        r_tok[nt] = (r / a.G) % a.N;
+        const long row = bwd_qrow(a, g, r), qr = row * D + 8 * hi;
+        const bool live = a.event_lens[r_stream[nt]] > 0;
+        l2[nt] = live ? a.lse[row] * kLog2eF : __builtin_inff();
+        dr[nt] = 0.f;
+#pragma unroll
+        for (int t = 0; t < KS; ++t) {
+            qB[nt][t] = *reinterpret_cast<const u32x4_t*>(a.q + qr + 16 * t);
+            dB[nt][t] = *reinterpret_cast<const u32x4_t*>(a.dout + qr + 16 * t);
         }
-        __syncthreads();
-        if (t + 1 < tiles) fetch(t + 1, kv, vv);  // next tile, in flight meanwhile
+        // D_i: the lane holds half of the row's elements, the lane 32 on the others
+        float sum = 0.f;
+#pragma unroll
+        for (int t = 0; t < KS; ++t) {
+            const u32x4_t x = *reinterpret_cast<const u32x4_t*>(a.out + qr + 16 * t);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                sum = fmaf(__uint_as_float(x[k] << 16), __uint_as_float(dB[nt][t][k] << 16), sum);
+                sum = fmaf(__uint_as_float(x[k] & 0xffff0000u), __uint_as_float(dB[nt][t][k] & 0xffff0000u), sum);
+            }
+        }
+        sum += __shfl_xor(sum, 32);
+        if (live) dr[nt] = sum;
+        if (a.row_splits == 1 && split == 0 && hi == 0 && 64 * w + 32 * nt + l32 < nrows)
+            a.drow[row] = live ? sum : __builtin_inff();  // for the dk, dv pass, which runs next
+    }
+    if (nst > 0) {
+#pragma unroll
+        for (int st = 0; st < NSTAGE - 1; ++st) issue_stage(st);
+    }
+    wait_vmcnt<0>();  // plain loads and DMA complete in no order relative to each other
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int t = 0; t < KS; ++t) asm volatile("" : "+a"(qB[nt][t]), "+a"(dB[nt][t]));
+    bf32x16_t acc[NT][DT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[nt][dt][i] = 0.f;
+    const BwdOffsets<D> off(lane);
 
+    for (int st = 0; st < nst; ++st) {
+        stage_barrier<2 * PPW>();
+        issue_stage(st + 3);
+        const UnitInfo ui = unit(at, u0 + st);
+        int lim[NT];  // visible keys of the lane's rows
+        bool any = false;
 #pragma unroll
-        for (int kb = (TK / 32) * kh; kb < (TK / 32) * (kh + 1); ++kb) {
-            // S^T = K Q^T, dP^T = V dO^T: lane holds keys 16 kb + 4 lg + i of row l16
-            f32x4_t s = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
+        for (int nt = 0; nt < NT; ++nt) {
+            lim[nt] = min(ui.nk, ui.stream < 0 ? kUnit : r_stream[nt] == ui.stream ? r_tok[nt] + 1 - ui.k0 : 0);
+            any |= lim[nt] > 0;
+        }
+        if (!active || !__any(any)) continue;
+        const unsigned char* kt = lds + (st % NSTAGE) * STAGE;
+        const unsigned char* vt = kt + TILE;
+#pragma unroll 1
+        for (int kb = 0; kb < kUnit; kb += 32) {
+            const unsigned char* kr = kt + kb * ROWB;
+            const unsigned char* vr = vt + kb * ROWB;
+            u32x4_t kf[KS], vf[KS], ds[NT][2];
+            bf32x16_t s[NT], dp[NT];
 #pragma unroll
-            for (int st = 0; st < KS; ++st) {
-                const u32x4_t ka = *reinterpret_cast<const u32x4_t*>(ks + tile_off<D>(16 * kb + l16, 4 * st + lg));
-                const u32x4_t va = *reinterpret_cast<const u32x4_t*>(vs + tile_off<D>(16 * kb + l16, 4 * st + lg));
-                s = mfma_16x16x32(as_bf16x8(ka), as_bf16x8(qB[st]), s);
-                dp = mfma_16x16x32(as_bf16x8(va), as_bf16x8(doB[st]), dp);
+            for (int t = 0; t < KS; ++t) {
+                kf[t] = bwd_read_row<D>(kr, off, t);
+                vf[t] = bwd_read_row<D>(vr, off, t);
             }
-            float ds[4];
+            auto scores = [&](int nt) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int kk = 16 * kb + 4 * lg + i;  // key within the tile
-                bool vis = kk < nv;
-                if (f >= 0) vis = vis & (f == re) & (t0 + kk <= rtok);
-                const float p = vis ? fast_exp2(fmaf(s[i], a.c, -l2)) : 0.f;
-                ds[i] = p * (dp[i] - dr);
-            }
-            const s16x4_t dsa = pack_bf16x4(ds[0], ds[1], ds[2], ds[3]);
+                for (int i = 0; i < 16; ++i) s[nt][i] = dp[nt][i] = 0.f;
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) acc[dt] = mfma_16x16x16(dsa, tile_tr<D>(ks, 16 * kb, dt, l16, lg), acc[dt]);
+                for (int t = 0; t < KS; ++t) {
+                    s[nt] = branch_mfma(kf[t], qB[nt][t], s[nt]);
+                    dp[nt] = branch_mfma(vf[t], dB[nt][t], dp[nt]);
+                }
+            };
+            auto soft = [&](int nt) __attribute__((always_inline)) {
+                const int lm = lim[nt] - kb - 4 * hi;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    float de[2];
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const int i = 2 * k + j;
+                        const float x = fmaf(s[nt][i], a.c, -l2[nt]);
+                        de[j] = fast_exp2(8 * (i >> 2) + (i & 3) < lm ? x : kNegInf) * (dp[nt][i] - dr[nt]);
+                    }
+                    ds[nt][k >> 2][k & 3] = pack_bf16x2(de[0], de[1]);
+                    if ((k & 3) == 3) asm volatile("" : "+v"(ds[nt][k >> 2]));  // computed in this phase
+                }
+            };
+            auto grads = [&](int nt) __attribute__((always_inline)) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int dt = 0; dt < DT; ++dt)
+                        acc[nt][dt] = branch_mfma(bwd_read_tr<D>(kr, off, q, dt), ds[nt][q], acc[nt][dt]);
+            };
+            scores(0);
+            __builtin_amdgcn_sched_barrier(0);
+            scores(1);
+            soft(0);
+            __builtin_amdgcn_sched_barrier(0);
+            grads(0);
+            soft(1);
+            __builtin_amdgcn_sched_barrier(0);
+            grads(1);
         }
     }
+    wait_vmcnt<0>();  // no DMA into the LDS outlives the work-group
 
-    // the second key half hands its sums to the first through LDS
-    f32x4_t* mbuf = reinterpret_cast<f32x4_t*>(lds);  // [4 row blocks][64 lanes][DT]
-    static_assert(4 * 64 * DT * 16 <= 2 * TK * 2 * D, "merge buffer");
-    __syncthreads();  // the tiles are no longer read
-    if (kh == 1) {
+    if (!active) return;
+    // lane: row 32 nt + l % 32, d 32 dt + 8 (i / 4) + 4 (l / 32) + i % 4
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) mbuf[(w * 64 + lane) * DT + dt] = acc[dt];
+    for (int nt = 0; nt < NT; ++nt) {
+        const int r = 64 * w + 32 * nt + l32;
+        if (r >= nrows) continue;
+        float* const base = split == 0 ? a.dq
+                            : split <= a.part_n ? a.part0 + (split - 1) * a.part_elems
+                                                : a.part1 + (split - 1 - a.part_n) * a.part_elems;
+        float* dst = base + bwd_qrow(a, g, row0 + r) * D + 4 * hi;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                *reinterpret_cast<f32x4_t*>(dst + 32 * dt + 8 * k) =
+                    f32x4_t{a.tau * acc[nt][dt][4 * k], a.tau * acc[nt][dt][4 * k + 1], a.tau * acc[nt][dt][4 * k + 2],
+                            a.tau * acc[nt][dt][4 * k + 3]};
     }
-    __syncthreads();
-    if (kh == 1) return;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) acc[dt] += mbuf[(w * 64 + lane) * DT + dt];
+}
 
-    // lane holds rows 16 w + 4 lg + i, d = 16 dt + l16
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = rw0 + 16 * w + 4 * lg + i;
-        if (r >= R) continue;
-        float* dst = a.dq + bwd_qrow(a, g, r) * D;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) dst[16 * dt + l16] = a.tau * acc[dt][i];
+// ---- 4: out += its later splits, in order; n4 float4 per tensor ----
+// y picks the tensor: out0, whose split k is float4 tensor (k - 1) step of
+// part0 (past part_n of them, of part1), or out1, each one tensor further on.
+__global__ __launch_bounds__(256) void bwd_sum_kernel(f32x4_t* out0, f32x4_t* out1, const f32x4_t* part0,
+                                                      const f32x4_t* part1, long n4, int step, int part_n, int splits)
+{
+    const long i = (long)wg_id() * 256 + wi_id();
+    if (i >= n4) return;
+    const int y = (int)__builtin_amdgcn_workgroup_id_y();
+    f32x4_t* const out = y > 0 ? out1 : out0;
+    f32x4_t s = out[i];
+    for (int k = 1; k < splits; ++k) {
+        const f32x4_t* p = k <= part_n ? part0 + (long)(k - 1) * step * n4 : part1 + (long)(k - 1 - part_n) * step * n4;
+        s += p[y * n4 + i];
     }
+    out[i] = s;
 }
 
 }  // namespace pdec
