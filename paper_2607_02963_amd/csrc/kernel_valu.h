@@ -1,17 +1,16 @@
-// Vector-ALU split pass: fewer query rows per kv head than one 16-row
-// matrix-core tile (bf16), and every float32 step.
+// Vector-ALU split pass (bf16, on request: tests and comparisons).
 //
 // Same work items as the matrix-core pass: (video, kv head, chunk of the
 // virtual key sequence, row group of RT = 8 rows; pdec_common.h).  The
 // work-group is 4 waves; wave w takes the chunk's units w, w+4, ... (64 keys
 // each) with its own online-softmax state, and the four states are merged in
-// LDS at the end.  Per unit, in both kernels:
+// LDS at the end.  Per unit:
 //   softmax lane = key; the wave max of a row (DPP) is only formed when some
 //           score exceeds the row's reference max by more than 8, which then
 //           becomes that max (O and l rescaled), as in the matrix-core pass;
 //   P V     lane = adjacent d, one coalesced V row per key load; the
 //           probabilities are broadcast LDS reads.
-// bf16 scores: a key row is split over LPK lanes of 32 bytes each (one pass
+// Scores: a key row is split over LPK lanes of 32 bytes each (one pass
 // covers 64/LPK keys); each lane keeps its 32-byte slice of the RT query
 // rows in registers for the whole item and forms partial dot products
 // through v_dot2c_f32_bf16 (exact products, float32 sums); the LPK partials
@@ -20,8 +19,6 @@
 // 2j, 2j + 1 are rounded to bf16 and packed into one word, and P V takes two
 // keys per v_dot2c_f32_bf16.  All K and V stays in registers, loaded one
 // unit ahead of its use.
-// float32 scores (the small-case precision path): lane = key, the key row in
-// registers and the query rows in LDS, read as broadcasts.
 // Keys past the unit's valid count, and for an own unit the rows of other
 // streams, get probability 0; reads of keys past the valid count are clamped
 // to the unit's last valid key, so nothing outside the unit is fetched.
@@ -440,149 +437,6 @@ __global__ __launch_bounds__(256) void split_valu_bf16_kernel(StepArgs a)
     }
 
     valu_merge_write<uint16_t, D, RT, DPL>(a, it, w, lane, true, lane * DPL, m_ref, l_lane, o, m_s, l_s, o_s[0], o_s[1],
-                                 o_s[2]);
-}
-
-// ----------------------------------------------------------------------------
-// float32, direct loads.
-template <int D, int RT, bool PLAN>
-__global__ __launch_bounds__(256) void split_valu_f32_kernel(StepArgs a)
-{
-    constexpr int NW = 4;
-    static_assert(RT == 8, "rows per item");
-    static_assert(D == 64 || D == 128, "head dim");
-    constexpr int ROWB = 4 * D;            // bytes per key row
-    constexpr int QW = ROWB / 16;          // 16-byte words per row
-    constexpr int KH = QW > 16 ? 16 : QW;  // words of a key row held at once
-    constexpr int NH = QW / KH;            // parts of a key row
-    constexpr int DPL = D / 64;            // d per lane in P V
-    constexpr int VB = 32;                 // keys of V held at once
-
-    __shared__ __attribute__((aligned(16))) uint4 q_s[RT][QW];
-    __shared__ __attribute__((aligned(16))) float p_s[NW][64 * RT];  // [key][row]
-    __shared__ __attribute__((aligned(16))) float o_s[NW - 1][RT * D];
-    __shared__ float m_s[NW][RT], l_s[NW][RT];
-    __shared__ int tab_start[kMaxStreamsPerVideo + 1];
-    __shared__ int tab_nlen[kMaxStreamsPerVideo];
-    __shared__ int s_total;
-
-    ValuItem it;
-    if (!valu_item<RT>(a, it, tab_start, tab_nlen, &s_total)) return;
-    const int tid = threadIdx.x;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lane = tid & 63;
-    const float c = a.qscale;
-    const uint32_t stride_b = (uint32_t)a.H_kv * ROWB;
-
-    int row_stream[RT];
-#pragma unroll
-    for (int r = 0; r < RT; ++r) row_stream[r] = r < it.nrows ? (it.row0 + r) / a.G : -2;
-    float* const pw = p_s[w];
-
-    // the item's query rows in LDS (rows past nrows are 0)
-    for (int i = tid; i < RT * QW; i += 256) {
-        const int r = i / QW;
-        uint4 x = make_uint4(0u, 0u, 0u, 0u);
-        if (r < it.nrows)
-            x = reinterpret_cast<const uint4*>(static_cast<const unsigned char*>(a.q) +
-                                               (long)row_qrow(a, it.vi, it.id.g, it.row0 + r) * ROWB)[i % QW];
-        q_s[r][i % QW] = x;
-    }
-    __syncthreads();
-
-    float m_ref[RT], l_lane[RT], o[RT][DPL];
-#pragma unroll
-    for (int r = 0; r < RT; ++r) {
-        m_ref[r] = -1e30f;
-        l_lane[r] = 0.f;
-#pragma unroll
-        for (int j = 0; j < DPL; ++j) o[r][j] = 0.f;
-    }
-
-    for (int u = it.u0 + w; u < it.u1; u += NW) {
-        const UnitInfo ui = uniform_unit(unit_info(a, it.vi, it.upre, tab_start, tab_nlen, it.id.g, u));
-        const int nk = ui.nk;
-        const unsigned char* kb =
-            static_cast<const unsigned char*>(ui.stream < 0 ? a.k_prefix : a.k_event) + ui.key_off * 4;
-        const unsigned char* vb =
-            static_cast<const unsigned char*>(ui.stream < 0 ? a.v_prefix : a.v_event) + ui.key_off * 4;
-
-        // ---- scores, lane = key: the key row in registers, KH words at a time ----
-        float sx[RT];
-#pragma unroll
-        for (int r = 0; r < RT; ++r) sx[r] = 0.f;
-        const AppendedKey ak = appended_key(a, it.vi, ui, it.id.g, 4);  // fused append: key from k_new / v_new
-        const int kk = min(lane, nk - 1);
-        const unsigned char* krow = kk == ak.key ? ak.krow : kb + (uint32_t)kk * stride_b;
-#pragma unroll
-        for (int h = 0; h < NH; ++h) {
-            uint4 kx[KH];
-#pragma unroll
-            for (int j = 0; j < KH; ++j) kx[j] = *reinterpret_cast<const uint4*>(krow + 16 * (h * KH + j));
-#pragma unroll
-            for (int j = 0; j < KH; ++j) {
-                int jj = h * KH + j;
-                asm volatile("" : "+s"(jj));
-#pragma unroll
-                for (int r = 0; r < RT; ++r) {
-                    const uint4 q = q_s[r][jj];
-                    sx[r] = fmaf(__uint_as_float(q.x), __uint_as_float(kx[j].x), sx[r]);
-                    sx[r] = fmaf(__uint_as_float(q.y), __uint_as_float(kx[j].y), sx[r]);
-                    sx[r] = fmaf(__uint_as_float(q.z), __uint_as_float(kx[j].z), sx[r]);
-                    sx[r] = fmaf(__uint_as_float(q.w), __uint_as_float(kx[j].w), sx[r]);
-                }
-#pragma unroll
-                for (int r = 0; r < RT; ++r) asm volatile("" : "+v"(sx[r]));
-            }
-        }
-
-        // ---- softmax per row, lane = key ----
-        {
-            const bool kvalid = lane < nk;
-            const bool plan_unit = PLAN && ui.stream < 0 && ui.k0 + kUnit > it.vi.plan0;  // self-only mask
-            float pv[RT];
-#pragma unroll
-            for (int r = 0; r < RT; ++r) {
-                bool row_sees = row_stream[r] != -2 && (ui.stream < 0 || row_stream[r] == ui.stream);
-                if (plan_unit) row_sees = row_sees & !plan_key_hidden(a, it.vi, ui.k0 + lane, row_stream[r]);
-                const float x = (kvalid && row_sees) ? sx[r] * c : kNegInf;
-                pv[r] = row_softmax<DPL>(x, m_ref[r], l_lane[r], o[r]);
-            }
-            float* dst = pw + lane * RT;
-            *reinterpret_cast<float4*>(dst) = make_float4(pv[0], pv[1], pv[2], pv[3]);
-            *reinterpret_cast<float4*>(dst + 4) = make_float4(pv[4], pv[5], pv[6], pv[7]);
-        }
-        wave_lds_sync();
-
-        // ---- P V: lane = DPL adjacent d, VB keys of V in flight ----
-#pragma unroll
-        for (int k0 = 0; k0 < kUnit; k0 += VB) {
-            if (k0 >= nk) continue;  // wave-uniform
-            float vf[VB][DPL];
-#pragma unroll
-            for (int k = 0; k < VB; ++k) {
-                const int kv = min(k0 + k, nk - 1);
-                const float* src =
-                    reinterpret_cast<const float*>(kv == ak.key ? ak.vrow : vb + (size_t)kv * stride_b) + lane * DPL;
-#pragma unroll
-                for (int j = 0; j < DPL; ++j) vf[k][j] = src[j];
-            }
-#pragma unroll
-            for (int k = 0; k < VB; ++k) {
-                const float* pr = pw + (k0 + k) * RT;
-                const float4 pa = *reinterpret_cast<const float4*>(pr);
-                const float4 pb = *reinterpret_cast<const float4*>(pr + 4);
-                const float pp[RT] = {pa.x, pa.y, pa.z, pa.w, pb.x, pb.y, pb.z, pb.w};
-#pragma unroll
-                for (int r = 0; r < RT; ++r)
-#pragma unroll
-                    for (int j = 0; j < DPL; ++j) o[r][j] = fmaf(pp[r], vf[k][j], o[r][j]);
-            }
-        }
-        wave_lds_sync();  // p_s is rewritten by the next unit
-    }
-
-    valu_merge_write<float, D, RT, DPL>(a, it, w, lane, true, lane * DPL, m_ref, l_lane, o, m_s, l_s, o_s[0], o_s[1],
                                  o_s[2]);
 }
 

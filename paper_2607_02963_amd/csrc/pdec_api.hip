@@ -23,6 +23,7 @@
 #include "pdec.h"
 
 #include "kernel_append.h"
+#include "kernel_f32.h"
 #include "kernel_finish.h"
 #include "kernel_rope.h"
 #include "kernel_valu.h"
@@ -254,7 +255,7 @@ Plan make_plan(const pdec_dims* d, int num_videos)
         if (ov == kPathMfma32 && d->head_dim == 128 && p.shape > 1) p.shape = p.shape == 2 ? 5 : 4;
     } else {
         p.shape = 0;
-        p.rows_per_item = 8;
+        p.rows_per_item = d->dtype == PDEC_DTYPE_BF16 ? 8 : rows_max > 16 ? 32 : 16;
     }
     p.rg_max = (int)ceil_div(rows_max, p.rows_per_item);
     // Units of the virtual key sequence of one (video, kv head): prefix units
@@ -268,9 +269,23 @@ Plan make_plan(const pdec_dims* d, int num_videos)
     const long units_expected = ceil_div(tokens, kUnitKeys) + own_expected;
     long upc = ceil_div(units_expected * d->num_kv_heads * p.rg_max, kTargetItems);
     if (path == kPathValu) {
-        // four waves per item, each taking every fourth unit: a multiple of 4
-        upc = std::max<long>(4, (units_expected * d->num_kv_heads * p.rg_max + 2 * kTargetItems) /
-                                    (4 * kTargetItems) * 4);
+        // bf16: four waves per item, each taking every fourth unit: a multiple of 4
+        const long rg8 = ceil_div(rows_max, 8);
+        const long upc8 =
+            std::max<long>(4, (units_expected * d->num_kv_heads * rg8 + 2 * kTargetItems) / (4 * kTargetItems) * 4);
+        if (d->dtype == PDEC_DTYPE_BF16) {
+            upc = upc8;
+        } else {
+            // float32: the four waves share every unit, and two items fit a
+            // compute unit; a single unit per chunk where there are few (the
+            // 256-key, 16-row step: 18.9 us with 4 units, see kernel_f32.h),
+            // but no more states than the scratch of pdec_attn_step_noalloc
+            // holds where the 8-row chunks above would stay within it
+            upc = std::max<long>(1, ceil_div(units_expected * d->num_kv_heads * p.rg_max, 2 * kTargetItems));
+            const double unit_bytes = (double)d->num_events * d->num_q_heads * (d->head_dim * 4.0 + 8.0);
+            while (upc < upc8 && ceil_div(units_max, upc) * unit_bytes + 4.0 * num_videos > (double)PDEC_NOALLOC_SCRATCH_BYTES)
+                ++upc;
+        }
     }
     upc = std::max<long>(upc, ceil_div(std::max<long>(units_max, 1), kMaxChunks));
     upc = std::max<long>(upc, 1);
@@ -316,20 +331,19 @@ int launch_status()
 
 // The self-only plan mask has kernels of its own, so that the full design's
 // inner loop carries none of its tests.
-template <typename T, int D, bool PLAN>
-void launch_valu_kernel(const StepArgs& a, int grid, hipStream_t s)
+template <int D, bool PLAN>
+void launch_vector_kernel(const StepArgs& a, bool bf16, int grid, hipStream_t s)
 {
-    if constexpr (std::is_same<T, uint16_t>::value)
-        hipLaunchKernelGGL((split_valu_bf16_kernel<D, 8, PLAN>), dim3(grid), dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL((split_valu_f32_kernel<D, 8, PLAN>), dim3(grid), dim3(256), 0, s, a);
+    if (bf16) hipLaunchKernelGGL((split_valu_bf16_kernel<D, 8, PLAN>), dim3(grid), dim3(256), 0, s, a);
+    else if (a.rows_per_item == 32) hipLaunchKernelGGL((split_f32_kernel<D, 2, PLAN>), dim3(grid), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((split_f32_kernel<D, 1, PLAN>), dim3(grid), dim3(256), 0, s, a);
 }
 
-template <typename T, int D>
-void launch_valu(const StepArgs& a, int grid, hipStream_t s)
+template <int D>
+void launch_vector(const StepArgs& a, bool bf16, int grid, hipStream_t s)
 {
-    if (a.plan_T > 0) launch_valu_kernel<T, D, true>(a, grid, s);
-    else launch_valu_kernel<T, D, false>(a, grid, s);
+    if (a.plan_T > 0) launch_vector_kernel<D, true>(a, bf16, grid, s);
+    else launch_vector_kernel<D, false>(a, bf16, grid, s);
 }
 
 // The device-length contract on host copies (pdec_check_lengths).
@@ -506,12 +520,9 @@ int run_step(const pdec_dims* d, int num_videos, const void* q, const void* k_pr
         launch_branch(a, p.own_bound, p.rows_first, s);
     } else if (p.path == kPathMfma) {
         launch_split_mfma(a, p.shape, grid, s);
-    } else if (bf16) {
-        if (d->head_dim == 128) launch_valu<uint16_t, 128>(a, grid, s);
-        else launch_valu<uint16_t, 64>(a, grid, s);
     } else {
-        if (d->head_dim == 128) launch_valu<float, 128>(a, grid, s);
-        else launch_valu<float, 64>(a, grid, s);
+        if (d->head_dim == 128) launch_vector<128>(a, bf16, grid, s);
+        else launch_vector<64>(a, bf16, grid, s);
     }
     if ((rc = launch_status()) != PDEC_OK) return rc;
     if (ev_stop && hipEventRecord(ev_stop, s) != hipSuccess) return PDEC_ERR_HIP;
