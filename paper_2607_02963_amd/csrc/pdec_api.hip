@@ -233,7 +233,8 @@ Plan make_plan(const pdec_dims* d, int num_videos)
     // bf16 runs on the matrix cores at any row count: a single-stream step
     // (7 rows per kv head) pads its 16-row tile and still takes about half
     // the time of the vector kernel (12.8 vs 22.7 us at a 16384-token
-    // prefix, measured); float32 has no matrix-core kernel
+    // prefix, measured); float32 has a kernel of its own (kernel_f32.h),
+    // planned as the vector path
     int path = d->dtype == PDEC_DTYPE_BF16 ? kPathMfma : kPathValu;
     const int ov = g_path_override.load();
     if (ov == kPathValu) path = kPathValu;
@@ -277,9 +278,10 @@ Plan make_plan(const pdec_dims* d, int num_videos)
             upc = upc8;
         } else {
             // float32: the four waves share every unit, and two items fit a
-            // compute unit; a single unit per chunk where there are few (the
-            // 256-key, 16-row step: 18.9 us with 4 units, see kernel_f32.h),
-            // but no more states than the scratch of pdec_attn_step_noalloc
+            // compute unit; a single unit per chunk where there are few (a
+            // 4095-key step of 13 streams: 27 us against 58 us for the
+            // vector kernel's chunks of four units and 8 rows), but no more
+            // states than the scratch of pdec_attn_step_noalloc
             // holds where the 8-row chunks above would stay within it
             upc = std::max<long>(1, ceil_div(units_expected * d->num_kv_heads * p.rg_max, 2 * kTargetItems));
             const double unit_bytes = (double)d->num_events * d->num_q_heads * (d->head_dim * 4.0 + 8.0);

@@ -176,12 +176,20 @@ def _dev(t: torch.Tensor, name: str, dtype=None, ndim=None):
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if ndim is not None and t.dim() != ndim:
         raise ValueError(f"{name} must have {ndim} dims, got {tuple(t.shape)}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()  # the argument types make pointers of plain integers
 
 
-def _stream(stream, device) -> ctypes.c_void_p:
-    s = stream if stream is not None else torch.cuda.current_stream(device)
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream(stream, device) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    return _raw_stream(device.index)
+
+
+# The current stream's handle on a device.  A step of a few microseconds on
+# the GPU is as long as its call on the host, and torch.cuda.current_stream
+# alone, which builds a Stream object, takes more than a tenth of that.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
+    (lambda index: torch.cuda.current_stream(index).cuda_stream)
 
 
 def make_dims(num_events, H_q, H_kv, D, cap, max_prefix_len, dtype_code, scale=0.0,
@@ -219,13 +227,13 @@ def set_path(path: int) -> int:
     return rc
 
 
-def _outputs(q, out, lse, workspace, ws_bytes):
+def _outputs(q, out, lse, workspace, dims, num_videos):
     if out is None:
         out = torch.empty_like(q)
     if lse is None:
         lse = torch.empty(q.shape[0], q.shape[1], dtype=torch.float32, device=q.device)
-    if workspace is None:
-        workspace = torch.empty(max(ws_bytes, 16), dtype=torch.uint8, device=q.device)
+    if workspace is None:  # a given one is measured by the call itself
+        workspace = torch.empty(max(workspace_size(dims, num_videos), 16), dtype=torch.uint8, device=q.device)
     return out, lse, workspace
 
 
@@ -247,13 +255,12 @@ def attn_step(q, k_prefix, v_prefix, k_event, v_event, event_lens, prefix_lens, 
         max_prefix_len = k_prefix.shape[0]
     dims = make_dims(E, H_q, H_kv, D, cap, max_prefix_len, _dtype_code(q), scale, plan_mask=plan_mask,
                      plan_per_stream=plan_per_stream)
-    ws_bytes = workspace_size(dims, 1)
-    out, lse, workspace = _outputs(q, out, lse, workspace, ws_bytes)
+    out, lse, workspace = _outputs(q, out, lse, workspace, dims, 1)
     args = [_dev(q, "q", ndim=3), _dev(k_prefix, "k_prefix", q.dtype, 3), _dev(v_prefix, "v_prefix", q.dtype, 3),
             _dev(k_event, "k_event", q.dtype, 4), _dev(v_event, "v_event", q.dtype, 4),
             _dev(event_lens, "event_lens", torch.int32, 1), _dev(prefix_lens, "prefix_lens", torch.int32, 1),
             _dev(out, "out", q.dtype, 3), _dev(lse, "lse", torch.float32, 2) if want_lse else None,
-            _dev(workspace, "workspace"), ctypes.c_size_t(workspace.numel() * workspace.element_size()),
+            _dev(workspace, "workspace"), workspace.nbytes,
             _stream(stream, q.device)]
     if v_prefix.shape != k_prefix.shape or v_event.shape != k_event.shape or k_event.shape[0] != E:
         raise ValueError("inconsistent K/V shapes")
@@ -308,13 +315,12 @@ def attn_prefill(q, k_prefix, v_prefix, k_event, v_event, event_lens, prefix_len
         max_prefix_len = k_prefix.shape[0]
     dims = make_dims(E, H_q, H_kv, D, cap, max_prefix_len, _dtype_code(q), scale, queries_per_stream=N,
                      cross_causal=cross)
-    ws_bytes = workspace_size(dims, 1)
     if out is None:
         out = torch.empty_like(q)
     if lse is None:
         lse = torch.empty((E, N, H_q), dtype=torch.float32, device=q.device)
     if workspace is None:
-        workspace = torch.empty(max(ws_bytes, 16), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(max(workspace_size(dims, 1), 16), dtype=torch.uint8, device=q.device)
     if v_prefix.shape != k_prefix.shape or v_event.shape != k_event.shape or k_event.shape[0] != E:
         raise ValueError("inconsistent K/V shapes")
     if event_lens.shape[0] != E or out.shape != q.shape or lse.shape != (E, N, H_q):
@@ -323,7 +329,7 @@ def attn_prefill(q, k_prefix, v_prefix, k_event, v_event, event_lens, prefix_len
             _dev(k_event, "k_event", q.dtype, 4), _dev(v_event, "v_event", q.dtype, 4),
             _dev(event_lens, "event_lens", torch.int32, 1), _dev(prefix_lens, "prefix_lens", torch.int32, 1),
             _dev(out, "out", q.dtype, 4), _dev(lse, "lse", torch.float32, 3),
-            _dev(workspace, "workspace"), ctypes.c_size_t(workspace.numel() * workspace.element_size()),
+            _dev(workspace, "workspace"), workspace.nbytes,
             _stream(stream, q.device)]
     _check("pdec_attn_step", lib().pdec_attn_step(ctypes.byref(dims), *args))
     return out, lse
@@ -345,8 +351,8 @@ def attn_prefill_backward(q, k_prefix, v_prefix, k_event, v_event, event_lens, p
     if max_prefix_len is None:
         max_prefix_len = k_prefix.shape[0]
     dims = make_dims(E, H_q, H_kv, D, cap, max_prefix_len, _dtype_code(q), scale, queries_per_stream=N)
-    ws_bytes = int(lib().pdec_backward_workspace_size(ctypes.byref(dims)))
     if workspace is None:
+        ws_bytes = int(lib().pdec_backward_workspace_size(ctypes.byref(dims)))
         workspace = torch.empty(max(ws_bytes, 16), dtype=torch.uint8, device=q.device)
     if out.shape != q.shape or dout.shape != q.shape or lse.shape != (E, N, H_q):
         raise ValueError("out / dout / lse shapes")
@@ -362,7 +368,7 @@ def attn_prefill_backward(q, k_prefix, v_prefix, k_event, v_event, event_lens, p
             _dev(out, "out", q.dtype, 4), _dev(lse, "lse", torch.float32, 3), _dev(dout, "dout", q.dtype, 4),
             _dev(dq, "dq"), _dev(dkp, "dk_prefix"), _dev(dvp, "dv_prefix"), _dev(dke, "dk_event"),
             _dev(dve, "dv_event"), _dev(workspace, "workspace"),
-            ctypes.c_size_t(workspace.numel() * workspace.element_size()), _stream(stream, q.device)]
+            workspace.nbytes, _stream(stream, q.device)]
     _check("pdec_attn_prefill_backward", lib().pdec_attn_prefill_backward(ctypes.byref(dims), *args))
     return dq, dkp, dvp, dke, dve
 
@@ -382,24 +388,23 @@ def attn_prefill_ragged(q, k_prefix, v_prefix, cu_prefix, k_event, v_event, even
     V = cu_prefix.shape[0] - 1
     dims = make_dims(SE, H_q, H_kv, D, cap, max_prefix_len, _dtype_code(q), scale, max_events_per_video,
                      prefix_tokens=k_prefix.shape[0], queries_per_stream=N, cross_causal=cross)
-    ws_bytes = workspace_size(dims, V)
     if out is None:
         out = torch.empty_like(q)
     if lse is None:
         lse = torch.empty((SE, N, H_q), dtype=torch.float32, device=q.device)
     if workspace is None:
-        workspace = torch.empty(max(ws_bytes, 16), dtype=torch.uint8, device=q.device)
+        workspace = torch.empty(max(workspace_size(dims, V), 16), dtype=torch.uint8, device=q.device)
     if cu_events.shape[0] != V + 1 or k_event.shape[0] != SE or event_lens.shape[0] != SE:
         raise ValueError("inconsistent batch shapes")
     if v_prefix.shape != k_prefix.shape or v_event.shape != k_event.shape or out.shape != q.shape \
             or lse.shape != (SE, N, H_q):
         raise ValueError("inconsistent K/V / out / lse shapes")
-    args = [ctypes.c_int32(V), _dev(q, "q", ndim=4), _dev(k_prefix, "k_prefix", q.dtype, 3),
+    args = [V, _dev(q, "q", ndim=4), _dev(k_prefix, "k_prefix", q.dtype, 3),
             _dev(v_prefix, "v_prefix", q.dtype, 3), _dev(cu_prefix, "cu_prefix", torch.int32, 1),
             _dev(k_event, "k_event", q.dtype, 4), _dev(v_event, "v_event", q.dtype, 4),
             _dev(event_lens, "event_lens", torch.int32, 1), _dev(cu_events, "cu_events", torch.int32, 1),
             _dev(out, "out", q.dtype, 4), _dev(lse, "lse", torch.float32, 3),
-            _dev(workspace, "workspace"), ctypes.c_size_t(workspace.numel() * workspace.element_size()),
+            _dev(workspace, "workspace"), workspace.nbytes,
             _stream(stream, q.device)]
     _check("pdec_attn_step_ragged", lib().pdec_attn_step_ragged(ctypes.byref(dims), *args))
     return out, lse
@@ -419,18 +424,17 @@ def attn_step_ragged(q, k_prefix, v_prefix, cu_prefix, k_event, v_event, event_l
     V = cu_prefix.shape[0] - 1
     dims = make_dims(SE, H_q, H_kv, D, cap, max_prefix_len, _dtype_code(q), scale, max_events_per_video,
                      prefix_tokens=k_prefix.shape[0], plan_mask=plan_mask, plan_per_stream=plan_per_stream)
-    ws_bytes = workspace_size(dims, V)
-    out, lse, workspace = _outputs(q, out, lse, workspace, ws_bytes)
+    out, lse, workspace = _outputs(q, out, lse, workspace, dims, V)
     if cu_events.shape[0] != V + 1 or k_event.shape[0] != SE or event_lens.shape[0] != SE:
         raise ValueError("inconsistent batch shapes")
     if v_prefix.shape != k_prefix.shape or v_event.shape != k_event.shape or out.shape != q.shape:
         raise ValueError("inconsistent K/V shapes")
-    args = [ctypes.c_int32(V), _dev(q, "q", ndim=3), _dev(k_prefix, "k_prefix", q.dtype, 3),
+    args = [V, _dev(q, "q", ndim=3), _dev(k_prefix, "k_prefix", q.dtype, 3),
             _dev(v_prefix, "v_prefix", q.dtype, 3), _dev(cu_prefix, "cu_prefix", torch.int32, 1),
             _dev(k_event, "k_event", q.dtype, 4), _dev(v_event, "v_event", q.dtype, 4),
             _dev(event_lens, "event_lens", torch.int32, 1), _dev(cu_events, "cu_events", torch.int32, 1),
             _dev(out, "out", q.dtype, 3), _dev(lse, "lse", torch.float32, 2) if want_lse else None,
-            _dev(workspace, "workspace"), ctypes.c_size_t(workspace.numel() * workspace.element_size()),
+            _dev(workspace, "workspace"), workspace.nbytes,
             _stream(stream, q.device)]
     _check("pdec_attn_step_ragged", lib().pdec_attn_step_ragged(ctypes.byref(dims), *args))
     return out, lse
@@ -457,15 +461,14 @@ def decode_step(q, k_prefix, v_prefix, k_new, v_new, k_event, v_event, lens_in, 
         max_prefix_len = k_prefix.shape[0]
     dims = make_dims(SE, H_q, H_kv, D, cap, max_prefix_len, _dtype_code(q), scale, max_events_per_video,
                      prefix_tokens=k_prefix.shape[0] if ragged else 0)
-    ws_bytes = workspace_size(dims, V)
-    out, lse, workspace = _outputs(q, out, lse, workspace, ws_bytes)
+    out, lse, workspace = _outputs(q, out, lse, workspace, dims, V)
     if k_new.shape != (SE, H_kv, D) or v_new.shape != k_new.shape or k_event.shape[0] != SE:
         raise ValueError("inconsistent append shapes")
     if v_prefix.shape != k_prefix.shape or v_event.shape != k_event.shape or out.shape != q.shape:
         raise ValueError("inconsistent K/V shapes")
     if lens_in.shape[0] != SE or lens_out.shape[0] != SE:
         raise ValueError("lens shape")
-    args = [ctypes.c_int32(V), _dev(q, "q", ndim=3), _dev(k_prefix, "k_prefix", q.dtype, 3),
+    args = [V, _dev(q, "q", ndim=3), _dev(k_prefix, "k_prefix", q.dtype, 3),
             _dev(v_prefix, "v_prefix", q.dtype, 3),
             None if ragged else _dev(prefix_lens, "prefix_lens", torch.int32, 1),
             _dev(cu_prefix, "cu_prefix", torch.int32, 1) if ragged else None,
@@ -475,7 +478,7 @@ def decode_step(q, k_prefix, v_prefix, k_new, v_new, k_event, v_event, lens_in, 
             _dev(lens_in, "lens_in", torch.int32, 1), _dev(lens_out, "lens_out", torch.int32, 1),
             None if live is None else _dev(live, "live", torch.int32, 1),
             _dev(out, "out", q.dtype, 3), _dev(lse, "lse", torch.float32, 2) if want_lse else None,
-            _dev(workspace, "workspace"), ctypes.c_size_t(workspace.numel() * workspace.element_size()),
+            _dev(workspace, "workspace"), workspace.nbytes,
             _stream(stream, q.device)]
     _check("pdec_decode_step", lib().pdec_decode_step(ctypes.byref(dims), *args))
     return out, lse
@@ -544,13 +547,13 @@ def segment_grounding(g, p, cu_seg, threshold, *, scores=None, salient=None, wor
         scores = torch.empty((K, S), dtype=torch.float32, device=g.device)
     if salient is None:
         salient = torch.empty((K, S), dtype=torch.uint8, device=g.device)
-    ws_bytes = int(lib().pdec_grounding_workspace_size(ctypes.byref(dims)))
     if workspace is None:
+        ws_bytes = int(lib().pdec_grounding_workspace_size(ctypes.byref(dims)))
         workspace = torch.empty(max(ws_bytes, 16), dtype=torch.uint8, device=g.device)
     args = [_dev(g, "g", None, 2), _dev(p, "p", g.dtype, 2), _dev(cu_seg, "cu_seg", torch.int32, 1),
-            ctypes.c_float(float(threshold)), _dev(scores, "scores", torch.float32, 2),
-            _dev(salient, "salient", torch.uint8, 2), ctypes.c_void_p(workspace.data_ptr()),
-            ctypes.c_size_t(workspace.numel() * workspace.element_size()), _stream(stream, g.device)]
+            float(threshold), _dev(scores, "scores", torch.float32, 2),
+            _dev(salient, "salient", torch.uint8, 2), workspace.data_ptr(),
+            workspace.nbytes, _stream(stream, g.device)]
     _check("pdec_segment_grounding", lib().pdec_segment_grounding(ctypes.byref(dims), *args))
     return scores, salient
 
@@ -597,13 +600,13 @@ def aggregate(g, x, cu_seg, salient, mode, *, scores=None, q=None, k=None, lse=N
     dims = aggr_dims(K, N, S, hidden, mode, H_q, H_kv, D, scale, _dtype_code(g))
     if out is None:
         out = torch.empty_like(g)
-    ws_bytes = int(lib().pdec_aggregation_workspace_size(ctypes.byref(dims)))
     if workspace is None:
+        ws_bytes = int(lib().pdec_aggregation_workspace_size(ctypes.byref(dims)))
         workspace = torch.empty(max(ws_bytes, 256), dtype=torch.uint8, device=g.device)
     args = [_dev(g, "g", None, 2), _dev(x, "x", g.dtype, 2), _dev(cu_seg, "cu_seg", torch.int32, 1),
             _dev(salient, "salient", torch.uint8, 2), ptr["scores"], ptr["q"], ptr["k"], ptr["lse"],
-            ptr["weights"], _dev(out, "out", g.dtype, 2), ctypes.c_void_p(workspace.data_ptr()),
-            ctypes.c_size_t(workspace.numel() * workspace.element_size()), _stream(stream, g.device)]
+            ptr["weights"], _dev(out, "out", g.dtype, 2), workspace.data_ptr(),
+            workspace.nbytes, _stream(stream, g.device)]
     _check("pdec_aggregate", lib().pdec_aggregate(ctypes.byref(dims), *args))
     return out
 
