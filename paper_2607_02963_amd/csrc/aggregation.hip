@@ -65,7 +65,7 @@ int launch_passes(const pdec::AggrArgs& a, int chunks, hipStream_t s)
     if (hipGetLastError() != hipSuccess) return PDEC_ERR_HIP;
     hipLaunchKernelGGL(pdec::aggr_segment_kernel, dim3(a.S, R), dim3(256), 0, s, a);
     if (hipGetLastError() != hipSuccess) return PDEC_ERR_HIP;
-    hipLaunchKernelGGL(pdec::aggr_event_kernel, dim3(a.K, R), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(pdec::aggr_event_kernel, dim3(a.K, (a.hidden / 8 + 63) / 64), dim3(256), 0, s, a);
     return hipGetLastError() == hipSuccess ? PDEC_OK : PDEC_ERR_HIP;
 }
 

@@ -25,8 +25,8 @@
 //     share a slot and there are at most chunks + S of them;
 //  3. segments: segment s adds its pieces over the chunks it spans, in chunk
 //     order;
-//  4. events: event i adds the sums of its salient segments in segment order,
-//     divides by their weight, adds g_i and rounds once to bf16.
+//  4. events: event i adds the sums of its salient segments, four interleaved
+//     runs in segment order, divides by their weight, adds g_i and rounds once to bf16.
 // Every sum has a fixed order, so repeated calls agree bit for bit.
 #pragma once
 
@@ -65,14 +65,26 @@ __device__ inline void aggr_segment_range(const AggrArgs& a, int s, int& lo, int
     hi = min(max(a.cu_seg[s + 1], lo), a.N);
 }
 
-__device__ inline void widen8(uint4 u, float* f)
+__device__ inline void widen8(u32x4_t u, float* f)
 {
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+    const uint32_t w[4] = {u[0], u[1], u[2], u[3]};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         f[2 * i] = __uint_as_float(w[i] << 16);
         f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
     }
+}
+
+__device__ inline void add8(float* acc, const float4* p)
+{
+    acc[0] += p[0].x;
+    acc[1] += p[0].y;
+    acc[2] += p[0].z;
+    acc[3] += p[0].w;
+    acc[4] += p[1].x;
+    acc[5] += p[1].y;
+    acc[6] += p[1].z;
+    acc[7] += p[1].w;
 }
 
 // ---- pass 1: head-averaged attention weights of the chunk's 64 tokens ----
@@ -96,7 +108,7 @@ __device__ inline void aggr_chunk_weights(const AggrArgs& a, int c, float* wl, f
             const uint16_t* row = a.k + ((long)min(tok, a.N - 1) * a.H_kv + gk) * D;
 #pragma unroll
             for (int t = 0; t < KSTEPS; ++t) {
-                kb[tt][t] = *reinterpret_cast<const u32x4_t*>(row + 32 * t + 8 * lg);
+                kb[tt][t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(row + 32 * t + 8 * lg));
                 if (tok >= a.N) kb[tt][t] = u32x4_t{0u, 0u, 0u, 0u};
             }
         }
@@ -149,6 +161,11 @@ __device__ inline void aggr_chunk_weights(const AggrArgs& a, int c, float* wl, f
 }
 
 // ---- pass 2: weighted sums of embedding rows per segment piece ----
+// Bound by HBM: embeddings and keys pass through once, so their loads are
+// nontemporal and leave the caches to the pieces, which pass 3 reads back
+// (32704 tokens x 3584, 268 MB: a call 62.9 us with ordinary loads, 55.9 with
+// these, 4.8 TB/s; a large copy moves 4.76.  Tokens that are in the caches
+// already, 1000 to 32704 of them: none slower).
 // Thread tid covers the 8-element vectors tid + 256 r, r < R, of a row.  DA
 // is the head width in attention mode (the weights come from pass 1, done
 // here first), 0 in the other modes.
@@ -209,16 +226,16 @@ __global__ __launch_bounds__(256) void aggr_pool_kernel(AggrArgs a)
     };
 
     for (int tb = t0; tb < t1; tb += U) {
-        uint4 xv[U][R];
+        u32x4_t xv[U][R];
         float wv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int t = min(tb + u, t1 - 1);  // clamped: every load stays inside the chunk
-            const uint4* row = reinterpret_cast<const uint4*>(a.x + (long)t * a.hidden);
+            const u32x4_t* row = reinterpret_cast<const u32x4_t*>(a.x + (long)t * a.hidden);
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int v = tid + 256 * r;
-                xv[u][r] = v < V8 ? row[v] : make_uint4(0u, 0u, 0u, 0u);
+                xv[u][r] = v < V8 ? __builtin_nontemporal_load(row + v) : u32x4_t{0u, 0u, 0u, 0u};
             }
             if constexpr (DA > 0) wv[u] = wl[t - c * kAggrChunk];
             else wv[u] = a.mode == kAggrModeUniform ? 1.f : a.scores[t];
@@ -266,21 +283,24 @@ __global__ __launch_bounds__(256) void aggr_segment_kernel(AggrArgs a)
     float ws = 0.f;
     if (hi > lo) {
         const int c0 = lo / kAggrChunk, c1 = min((hi - 1) / kAggrChunk, nchunks - 1);
-        for (int c = c0; c <= c1; ++c) {
-            const long slot = (long)c + s;
-            if (live) {
-                const float4* src = reinterpret_cast<const float4*>(a.piece + slot * a.hidden + 8 * v);
-                const float4 p0 = src[0], p1 = src[1];
-                acc[0] += p0.x;
-                acc[1] += p0.y;
-                acc[2] += p0.z;
-                acc[3] += p0.w;
-                acc[4] += p1.x;
-                acc[5] += p1.y;
-                acc[6] += p1.z;
-                acc[7] += p1.w;
+        for (int c = c0; c <= c1; c += 4) {  // four pieces in flight (indices clamped), added in order
+            float4 p[4][2];
+            float pw[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const long slot = (long)min(c + u, c1) + s;
+                const float4* src =
+                    reinterpret_cast<const float4*>(a.piece + slot * a.hidden + 8 * min(v, a.hidden / 8 - 1));
+                p[u][0] = src[0];
+                p[u][1] = src[1];
+                pw[u] = a.piece_w[slot];
             }
-            ws += a.piece_w[slot];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (c + u > c1) break;
+                add8(acc, p[u]);
+                ws += pw[u];
+            }
         }
     }
     if (live) {
@@ -292,17 +312,21 @@ __global__ __launch_bounds__(256) void aggr_segment_kernel(AggrArgs a)
 }
 
 // ---- pass 4: per event, the salient segments' sums over their weight ----
-// Work-group (i, y) covers the 8-element vectors 256 y + tid of event i.  The
+// Work-group (i, y) covers the 8-element vectors 64 y + lane of event i.  The
 // salient segments are listed in LDS 256 at a time (ballot and prefix count,
-// so the list keeps segment order), then their sums are added four loads at
-// a time.
+// so the list keeps segment order); wave w adds the sums of entries w, w + 4,
+// ... four loads at a time, and the four waves meet in a fixed order.  Bound by
+// memory round trips: with 256 vectors per work-group and one wave per vector,
+// 64 work-groups went through four times the serial loads (with the four
+// pieces in flight of pass 3: a call 65.2 -> 62.9 us at 32704 tokens).
 __global__ __launch_bounds__(256) void aggr_event_kernel(AggrArgs a)
 {
     __shared__ int list[256];
     __shared__ int wave_count[4];
+    __shared__ float part[3][9][64];  // waves 1 .. 3: eight sums and the weight
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
-    const int v = 256 * blockIdx.y + tid;
+    const int v = 64 * blockIdx.y + lane;
     const bool live = v < a.hidden / 8;
     const int i = blockIdx.x;
     const uint8_t* sal = a.salient + (long)i * a.S;
@@ -324,34 +348,38 @@ __global__ __launch_bounds__(256) void aggr_event_kernel(AggrArgs a)
         }
         if (f) list[before] = s;
         __syncthreads();
-        for (int j = 0; j < n; j += 4) {
+        for (int j = wave; j < n; j += 16) {
             float4 p[4][2];
+            float pw[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int sj = list[min(j + u, n - 1)];
+                const int sj = list[min(j + 4 * u, n - 1)];
                 const float4* src = reinterpret_cast<const float4*>(a.seg + (long)sj * a.hidden + 8 * min(v, a.hidden / 8 - 1));
                 p[u][0] = src[0];
                 p[u][1] = src[1];
+                pw[u] = a.seg_w[sj];
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                if (j + u >= n) break;
-                acc[0] += p[u][0].x;
-                acc[1] += p[u][0].y;
-                acc[2] += p[u][0].z;
-                acc[3] += p[u][0].w;
-                acc[4] += p[u][1].x;
-                acc[5] += p[u][1].y;
-                acc[6] += p[u][1].z;
-                acc[7] += p[u][1].w;
-                ws += a.seg_w[list[j + u]];
+                if (j + 4 * u >= n) break;
+                add8(acc, p[u]);
+                ws += pw[u];
             }
         }
         __syncthreads();  // the list is rewritten by the next batch
     }
-    if (!live) return;
-    const uint4 gv = reinterpret_cast<const uint4*>(a.g + (long)i * a.hidden)[v];
-    uint4 o = gv;  // an empty selection leaves g_i as it is
+    if (wave > 0) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) part[wave - 1][e][lane] = acc[e];
+        part[wave - 1][8][lane] = ws;
+    }
+    __syncthreads();
+    if (wave > 0 || !live) return;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = (acc[e] + part[0][e][lane]) + (part[1][e][lane] + part[2][e][lane]);
+    ws = (ws + part[0][8][lane]) + (part[1][8][lane] + part[2][8][lane]);
+    const u32x4_t gv = reinterpret_cast<const u32x4_t*>(a.g + (long)i * a.hidden)[v];
+    u32x4_t o = gv;  // an empty selection leaves g_i as it is
     if (ws != 0.f) {
         float f[8];
         widen8(gv, f);
@@ -362,9 +390,9 @@ __global__ __launch_bounds__(256) void aggr_event_kernel(AggrArgs a)
             const float hi = f[2 * e + 1] + acc[2 * e + 1] / ws;
             pk[e] = (uint32_t)from_f32<uint16_t>(lo) | ((uint32_t)from_f32<uint16_t>(hi) << 16);
         }
-        o = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+        o = u32x4_t{pk[0], pk[1], pk[2], pk[3]};
     }
-    reinterpret_cast<uint4*>(a.out + (long)i * a.hidden)[v] = o;
+    reinterpret_cast<u32x4_t*>(a.out + (long)i * a.hidden)[v] = o;
 }
 
 }  // namespace pdec

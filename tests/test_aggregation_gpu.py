@@ -152,3 +152,19 @@ def test_aggregation_in_place_and_repeatable():
 def test_aggregation_explicit_scale():
     w = wl.make_aggregation(K=4, N=500, S=6, hidden=256, H_q=4, H_kv=2, D=128, seed=11)
     _check(w, "attention", scale=0.05)
+
+
+@pytest.mark.parametrize("S,hidden", [(15, 504), (16, 512), (17, 520), (64, 1032), (257, 2056), (4097, 64)])
+def test_aggregation_many_salient_segments(S, hidden):
+    """Every count of listed segments left over by four waves of four loads,
+    lists longer than one 256-entry batch, 64-vector slices with a remainder,
+    and segment counts at the edges of the 64-way search."""
+    sizes = np.random.default_rng(S).integers(0, 3, S).tolist()
+    sizes[-1] += 300  # five or six chunks: a remainder of the four pieces in flight
+    w = wl.make_aggregation(K=20, N=sum(sizes), S=S, hidden=hidden, H_q=4, H_kv=2, D=64, seed=S, sizes=sizes, max_run=6)
+    w.salient[:] = 0
+    for i in range(20):
+        w.salient[i, max(0, S - i - 1):] = 1
+    w.salient[19, :] = 1
+    for mode in ("learned", "attention"):
+        _check(w, mode)
