@@ -73,6 +73,8 @@ __device__ inline int branch_vswz(int key)
 // lanes is the set of lanes that load, all or none: a piece without lanes
 // moves nothing but counts as one on the wave's counter.  Called with every
 // lane of the wave active.
+// Its base comes from scalar arithmetic, far from any vector write of an SGPR
+// (which the load would have to follow by five wait states).
 __device__ inline void dma_16B_m0(const void* base, uint32_t off, uint32_t lds_base, uint64_t lanes)
 {
     const uint64_t sb = sgpr_base(base);

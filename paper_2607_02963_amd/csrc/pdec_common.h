@@ -407,8 +407,10 @@ __device__ inline void dma_16B_sbase(const void* base, uint32_t off, uint32_t ld
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
     const uint64_t sb = ((uint64_t)hi << 32) | (uint64_t)lo;
     base = reinterpret_cast<const void*>(sb);
+    // five wait states between the readfirstlane that may be right before and
+    // the load that reads its SGPR (two moves, three of the s_nop)
     uint32_t saved;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 2\n\tglobal_load_lds_dwordx4 %2, %3\n\ts_mov_b32 m0, %0"
                  : "=&s"(saved)
                  : "s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(off), "s"(base)
                  : "memory");
