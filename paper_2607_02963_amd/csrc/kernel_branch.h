@@ -35,6 +35,7 @@
 #pragma once
 
 #include "kernel_mfma.h"
+#include "ring.h"
 
 namespace pdec {
 
@@ -70,8 +71,7 @@ __device__ inline int branch_vswz(int key)
 // offsets into LDS, M0 left changed (dma_16B_sbase restores it; a reserved
 // register, which the compiler sets right before each instruction of its own
 // that reads it).
-// lanes is the set of lanes that load, all or none: a piece without lanes
-// moves nothing but counts as one on the wave's counter.  Called with every
+// lanes is the set of lanes that load, never empty (ring.h).  Called with every
 // lane of the wave active.
 // Its base comes from scalar arithmetic, far from any vector write of an SGPR
 // (which the load would have to follow by five wait states).
@@ -233,13 +233,13 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
         choff[i] = 16u * ((lane % C::CH) ^ (w_is_v ? branch_vswz<D>(key) : branch_kswz<D>(key)));
     }
     const uint32_t m_base = lds_u32(lds) + (w_is_v ? C::STAGE_K : 0) + pk0 * 1024;
-    // Stages past the last are pieces without lanes, so that every wait below
+    // Stages past the last are pieces of one lane, so that every wait below
     // counts the same pieces.
     struct Pending { const uint16_t* base; uint32_t dst; int nk; uint64_t lanes; };
     auto pending = [&](int st) __attribute__((always_inline)) {
         const UnitInfo ui = unit(u0 + min(st, nst - 1));
         return Pending{reinterpret_cast<const uint16_t*>(pre + (ui.stream < 0 ? 0 : evt_pre) + 2 * ui.key_off),
-                       m_base + (st % C::NSTAGE) * C::STAGE, ui.nk, st < nst ? ~0ull : 0ull};
+                       m_base + (st % C::NSTAGE) * C::STAGE, ui.nk, ring_lanes(st, nst)};
     };
     auto issue_piece = [&](const Pending& pd, int i) __attribute__((always_inline)) {
         // keys past the last valid one re-read it (their scores are masked)

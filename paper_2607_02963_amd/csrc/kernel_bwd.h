@@ -83,8 +83,8 @@ __device__ inline long bwd_qrow(const BwdArgs& a, int g, int r)
     return (long)(r / a.G) * a.H_q + g * a.G + r % a.G;
 }
 
-// One float per lane straight into LDS, lane l's at lds_base + 4 l; lanes as
-// for dma_16B_m0.
+// One float per lane straight into LDS, lane l's at lds_base + 4 l; as
+// dma_16B_m0 otherwise.
 __device__ inline void dma_4B_m0(const void* base, uint32_t off, uint32_t lds_base, uint64_t lanes)
 {
     const uint64_t sb = sgpr_base(base);
@@ -201,12 +201,13 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel(BwdArgs a)
     // a key's rows start at rmin: own row t is seen by tokens j >= t
     const int rmin = prefix ? 0 : own * NG + (k0 + 32 * w + l32) * a.G;
 
-    // ---- DMA of one stage: waves 0, 1 Q rows, waves 2, 3 dO rows; wave 0 also lse, wave 1 D ----
+    // ---- DMA of one stage: waves 0, 1 Q rows, waves 2, 3 dO rows; waves 0, 2 also a half of lse, waves 1, 3 of D ----
     const bool w_is_d = w >= 2;
     const uint64_t qb = sgpr_base(a.q), db = sgpr_base(a.dout);
     const uint64_t src = w_is_d ? db : qb;
     const uint64_t lseb = sgpr_base(a.lse), drowb = sgpr_base(a.drow);
-    const uint64_t rvb = w == 0 ? lseb : drowb;
+    const uint64_t rvb = (w & 1) == 0 ? lseb : drowb;
+    const int rv0 = 32 * (w >> 1);  // first row value of the wave; lanes 0 .. 31 load
     const int row0 = (w & 1) * PPW * KPI + lane / CH;
     uint32_t choff[4];
 #pragma unroll
@@ -214,8 +215,8 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel(BwdArgs a)
     const float inv_g = 1.f / (float)a.G;
     const uint32_t lds0 = lds_u32(lds) + (w_is_d ? TILE : 0) + (w & 1) * PPW * 1024;
     auto issue_stage = [&](int st) __attribute__((always_inline)) {
-        const uint64_t lanes = st < nst ? ~0ull : 0ull;
-        const int rb = r_begin + 64 * min(st, max(nst - 1, 0));
+        const uint64_t lanes = ring_lanes(st, nst);
+        const int rb = r_begin + 64 * min(st, nst - 1);
         const int t0 = rb / a.G, h0 = rb - t0 * a.G;
         const uint64_t base = src + 2 * D * ((long)t0 * a.H_q + g * a.G);
         const uint32_t dst = lds0 + (st % NSTAGE) * STAGE;
@@ -227,10 +228,10 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel(BwdArgs a)
             const uint32_t off = (uint32_t)(t * a.H_q + n - t * a.G) * (2 * D) + choff[i & 3];
             dma_16B_m0(reinterpret_cast<const void*>(base), off, dst + 1024 * i, lanes);
         }
-        const int n = h0 + min(lane, r_end - 1 - rb);
+        const int n = h0 + min(rv0 + lane, r_end - 1 - rb);
         const int t = (int)(((float)n + 0.5f) * inv_g);
         dma_4B_m0(reinterpret_cast<const void*>(rvb + 4 * ((long)t0 * a.H_q + g * a.G)), 4 * (t * a.H_q + n - t * a.G),
-                  lds_u32(rowv[st % NSTAGE][w & 1]), w < 2 ? lanes : 0ull);
+                  lds_u32(rowv[st % NSTAGE][w & 1] + rv0), lanes & 0xffffffffull);
     };
 
     // The row values of a landed stage made ready, by wave 0, one barrier
@@ -259,8 +260,10 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel(BwdArgs a)
             }
         }
     }
+    if (nst > 0) {
 #pragma unroll
-    for (int st = 0; st < NSTAGE - 1; ++st) issue_stage(st);
+        for (int st = 0; st < NSTAGE - 1; ++st) issue_stage(st);
+    }
     wait_vmcnt<0>();  // plain loads and DMA complete in no order relative to each other
 #pragma unroll
     for (int t = 0; t < KS; ++t) asm volatile("" : "+a"(kB[t]), "+a"(vB[t]));
@@ -407,7 +410,7 @@ __global__ __launch_bounds__(256) void bwd_dq_kernel(BwdArgs a)
     for (int i = 0; i < 4; ++i) choff[i] = 16u * ((lane % CH) ^ bwd_swz<D>(key0 + i * KPI));
     const uint32_t lds0 = lds_u32(lds) + (w_is_v ? TILE : 0) + (w & 1) * PPW * 1024;
     auto issue_stage = [&](int st) __attribute__((always_inline)) {
-        const uint64_t lanes = st < nst ? ~0ull : 0ull;
+        const uint64_t lanes = ring_lanes(st, nst);
         const UnitInfo ui = unit(dma_at, u0 + min(st, nst - 1));
         const void* base = reinterpret_cast<const void*>(pre + (ui.stream < 0 ? 0 : evt_pre) + 2 * ui.key_off);
 #pragma unroll
