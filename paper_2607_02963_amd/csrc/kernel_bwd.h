@@ -11,7 +11,7 @@
 //
 // Passes, on v_mfma_f32_32x32x16_bf16 (1 only where 2 runs before 3, which
 // otherwise leaves D itself):
-//  1. per row: D_i, infinite for the rows of ended streams;
+//  1. per row: D_i, a mark for the rows of ended streams (bwd_drow_word);
 //  2. dk, dv: a work-group holds 128 keys of one kv head (32 per wave, K and V
 //     as B operands in registers) and walks the rows that see them in stages
 //     of 64.  S = Q K^T and dP = dO V^T give a lane one key and 16 rows of a
@@ -55,7 +55,7 @@ struct BwdArgs {
     const uint16_t* out;   // [E, N, H_q, D]
     const float* lse;      // [E, N, H_q]
     const uint16_t* dout;  // [E, N, H_q, D]
-    float* drow;           // [E, N, H_q]: D, +inf for the rows of ended streams
+    float* drow;           // [E, N, H_q]: D, or the mark of an ended stream's row
     float* dq;             // [E, N, H_q, D]
     float* dkp;            // [Lmax, H_kv, D]
     float* dvp;
@@ -81,6 +81,16 @@ struct BwdArgs {
 __device__ inline long bwd_qrow(const BwdArgs& a, int g, int r)
 {
     return (long)(r / a.G) * a.H_q + g * a.G + r % a.G;
+}
+
+// Row values between the passes: D, or kEndedRow for the row of an ended
+// stream.  The mark is a NaN that no D is: a live row may have any D, infinite
+// or NaN, and its NaN is stored as the plain quiet one.
+constexpr uint32_t kEndedRow = 0x7fc00001u;
+__device__ inline float bwd_drow_word(float D, bool live)
+{
+    const uint32_t u = __float_as_uint(D);
+    return __uint_as_float(!live ? kEndedRow : (u & 0x7fffffffu) > 0x7f800000u ? 0x7fc00000u : u);
 }
 
 // One float per lane straight into LDS, lane l's at lds_base + 4 l; as
@@ -157,7 +167,7 @@ __global__ __launch_bounds__(256) void bwd_drow_kernel(BwdArgs a)
 #pragma unroll
     for (int off = 8; off > 0; off >>= 1) s += __shfl_xor(s, off);
     const bool live = a.event_lens[i / ((long)a.N * a.H_q)] > 0;
-    if (l == 0) a.drow[i] = live ? s : __builtin_inff();
+    if (l == 0) a.drow[i] = bwd_drow_word(s, live);
 }
 
 // ---- 2: dk, dv per 128 keys ----
@@ -240,7 +250,7 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel(BwdArgs a)
     auto row_values = [&](int st) __attribute__((always_inline)) {
         float* const v = rowv[st % NSTAGE][0] + lane;
         const float l = v[0], dr = v[64];
-        const bool none = dr == __builtin_inff() || r_begin + 64 * st + lane >= r_end;
+        const bool none = __float_as_uint(dr) == kEndedRow || r_begin + 64 * st + lane >= r_end;
         v[0] = none ? __builtin_inff() : l * kLog2eF;
         v[64] = none ? 0.f : dr;
     };
@@ -452,7 +462,7 @@ __global__ __launch_bounds__(256) void bwd_dq_kernel(BwdArgs a)
         sum += __shfl_xor(sum, 32);
         if (live) dr[nt] = sum;
         if (a.row_splits == 1 && split == 0 && hi == 0 && 64 * w + 32 * nt + l32 < nrows)
-            a.drow[row] = live ? sum : __builtin_inff();  // for the dk, dv pass, which runs next
+            a.drow[row] = bwd_drow_word(sum, live);  // for the dk, dv pass, which runs next
     }
     if (nst > 0) {
 #pragma unroll

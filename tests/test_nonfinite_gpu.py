@@ -1,0 +1,50 @@
+"""Infinities and NaN stay where the mask lets them go.
+
+A live row whose <dO, O> overflows is a live row: its gradient shows it.
+"""
+import numpy as np
+import pytest
+import torch
+
+import backward
+import oracle
+from gpu_util import dev_float, dev_int
+from paper_2607_02963_amd import pdec
+from paper_2607_02963_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("E,N,L,lens,H_q,H_kv,D", [
+    (3, 40, 300, [40, 0, 33], 4, 2, 128),
+    (5, 52, 257, [52, 3, 52, 52, 0], 5, 1, 128),   # many rows over few keys
+    (2, 5, 4000, [5, 4], 6, 2, 64),                # few rows over many keys
+    (1, 129, 0, [129], 7, 1, 128),                 # a causal sequence
+])
+def test_a_live_row_whose_output_product_overflows_stays_live(E, N, L, lens, H_q, H_kv, D):
+    """<dO, O> = +inf in one row: its p dO reaches dv, which stays finite and right, and its ds makes dk show it."""
+    rng = np.random.default_rng(17 + N)
+    f = lambda s, *shape: wl.bf16_bits((s * rng.standard_normal(shape)).astype(np.float32))  # noqa: E731
+    q, kp, vp = f(1.0, E, N, H_q, D), f(1.0, L, H_kv, D), f(0.5, L, H_kv, D)
+    ke, ve, do = f(1.0, E, N, H_kv, D), f(0.5, E, N, H_kv, D), f(0.5, E, N, H_q, D)
+    n = np.asarray(lens, np.int32)
+    out, lse = oracle.attn_prefill(q, kp, vp, ke, ve, n, [0, L], [0, E])
+    out_b, lse_f = wl.bf16_bits(out.astype(np.float32)), lse.astype(np.float32)
+    j = 3
+    out_b[0, j, 0, 0] = wl.bf16_bits(np.asarray([4.0], np.float32))[0]
+    do[0, j, 0, 0] = wl.bf16_bits(np.asarray([2.0e38], np.float32))[0]  # 8e38: past the largest float32
+    d = [dev_float(x, "bf16") for x in (q, kp, vp, ke, ve)]
+    g = pdec.attn_prefill_backward(*d, dev_int(n), dev_int([L]), dev_float(out_b, "bf16"),
+                                   torch.from_numpy(np.ascontiguousarray(lse_f)).cuda(), dev_float(do, "bf16"))
+    torch.cuda.synchronize()
+    ref = backward.attn_prefill_backward(q, kp, vp, ke, ve, n, out_b, lse_f, do)
+    for i, name in ((2, "dv_prefix"), (4, "dv_event")):
+        got, r = g[i].cpu().numpy().astype(np.float64), np.asarray(ref[i], np.float64).reshape(g[i].shape)
+        assert np.isfinite(got).all(), name
+        # p is rounded to bf16: 2^-9 relative in the one term that rules the norm, at most 2^-8
+        assert np.linalg.norm(got - r) <= 1e-2 * np.linalg.norm(r) + 1e-12, name
+    assert not torch.isfinite(g[0][0, j, 0]).any()
+    if L:
+        assert not torch.isfinite(g[1][:, 0]).any()
+        assert torch.isfinite(g[1][:, 1:]).all()
+    assert not torch.isfinite(g[3][0, :min(j + 1, lens[0]), 0]).any()
