@@ -210,6 +210,9 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel(BwdArgs a)
     nst = __builtin_amdgcn_readfirstlane(nst);
     // a key's rows start at rmin: own row t is seen by tokens j >= t
     const int rmin = prefix ? 0 : own * NG + (k0 + 32 * w + l32) * a.G;
+    // stages whose rows see none of the wave's keys: left out, so that what
+    // they hold (0 times an infinite dO is NaN) stays with the keys they see
+    const int skip = prefix ? 0 : max(own * NG + (k0 + 32 * w) * a.G - r_begin, 0) / 64;
 
     // ---- DMA of one stage: waves 0, 1 Q rows, waves 2, 3 dO rows; waves 0, 2 also a half of lse, waves 1, 3 of D ----
     const bool w_is_d = w >= 2;
@@ -286,11 +289,16 @@ __global__ __launch_bounds__(256) void bwd_dkdv_kernel(BwdArgs a)
 
     lds_barrier();  // every wave's pieces of the first stages have landed
     if (w == 0 && nst > 0) row_values(0);
-    for (int st = 0; st < nst; ++st) {
+    auto enter = [&](int st) __attribute__((always_inline)) {
         // stage st + 1 has landed too
         stage_barrier<PPW + 1>();
         issue_stage(st + 3);
         if (w == 0 && st + 1 < nst) row_values(st + 1);
+    };
+    int st = 0;
+    for (; st < min(skip, nst); ++st) enter(st);
+    for (; st < nst; ++st) {
+        enter(st);
         const unsigned char* qt = lds + (st % NSTAGE) * STAGE;
         const unsigned char* dt_ = qt + TILE;
         const int lo0 = rmin - (r_begin + 64 * st) - 4 * hi;

@@ -1,6 +1,10 @@
 """Infinities and NaN stay where the mask lets them go.
 
-A live row whose <dO, O> overflows is a live row: its gradient shows it.
+A masked key has probability 0, but 0 times an infinite or NaN value is NaN, so
+a work-group that multiplies a value row for some of its query rows can spoil
+the others.  The runs below differ from a finite run in one place; the outputs
+that do not see that place have to keep their bits.  And a live row whose
+<dO, O> overflows is a live row: its gradient shows it.
 """
 import numpy as np
 import pytest
@@ -13,6 +17,38 @@ from paper_2607_02963_amd import pdec
 from paper_2607_02963_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
+
+
+VALUES = [float("nan"), float("inf")]
+
+
+def _normal(seed, shape, sigma=1.0, dtype=torch.bfloat16):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return (torch.randn(shape, generator=g, device="cuda") * sigma).to(dtype)
+
+
+def _same(a, b):
+    return torch.equal(a, b) and bool(torch.isfinite(b).all())
+
+
+@pytest.mark.parametrize("bad", VALUES)
+def test_a_row_gradient_reaches_only_key_units_it_may_see(bad):
+    """dO of an early token is not finite: the cache rows of later 64-key units, which it does not see, keep their
+    gradients (a 128-key tile walks the rows of both of its units)."""
+    N, H, D = 192, 2, 128
+    q, do = _normal(1, (1, N, H, D)), _normal(2, (1, N, H, D), 0.5)
+    kp = vp = torch.empty((0, H, D), dtype=torch.bfloat16, device="cuda")
+    ke, ve, n, plen = _normal(3, (1, N, H, D)), _normal(4, (1, N, H, D), 0.5), dev_int([N]), dev_int([0])
+    out, lse = pdec.attn_prefill(q, kp, vp, ke, ve, n, plen)
+    do2 = do.clone()
+    do2[0, 10] = bad
+    a = pdec.attn_prefill_backward(q, kp, vp, ke, ve, n, plen, out, lse, do)
+    b = pdec.attn_prefill_backward(q, kp, vp, ke, ve, n, plen, out, lse, do2)
+    torch.cuda.synchronize()
+    assert not torch.isfinite(b[0][0, 10]).any() and _same(a[0][0, 11:], b[0][0, 11:]) and _same(a[0][0, :10], b[0][0, :10])
+    for g in (3, 4):
+        assert not torch.isfinite(b[g][0, :11]).any()
+        assert _same(a[g][0, 64:], b[g][0, 64:])
 
 
 @pytest.mark.parametrize("E,N,L,lens,H_q,H_kv,D", [
