@@ -279,7 +279,7 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
         for (int t = 0; t < C::KS; ++t) asm volatile("" : "+a"(qf[nt][t]));
 
     bf32x16_t o[NT][C::DT];
-    f32x4_t lsum[NT];
+    f32x4_t lsum[NT];  // four times the lane's sum
     float m_ref[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -330,17 +330,19 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
         const int s = i / (C::DT * NT), dt = (i / NT) % C::DT, nt = i % NT;
         o[nt][dt] = branch_mfma(v_op(vf, s, dt), pk[nt][s], o[nt][dt]);
     };
-    // The row sums of P (the rounded P, the one that meets V) are 16x16x32
-    // products with a selector: a P operand of the 32x32x16 product read as
-    // the 32 x 16 B operand has row l % 16 of the tile in lane groups 0 and 2
-    // and row 16 + l % 16 in groups 1 and 3; selector rows 0-7 add the former,
-    // rows 8-15 the latter, so lane l ends with the sum of tile row
-    // l % 16 + 16 (l / 32).  (v_dot2_f32_bf16 holds up the matrix cores: four
-    // of them beside a 32x32x16 product take 29 ns, four v_fma_f32 17 ns.)
-    const uint32_t sel_w = ((lane & 15) < 8) == ((lane & 16) == 0) ? 0x3f803f80u : 0u;
-    const bf16x8_t sel = as_bf16x8(u32x4_t{sel_w, sel_w, sel_w, sel_w});
+    // The row sums of P (the rounded P, the one that meets V), each lane over
+    // its own keys, four at a time, i = 0 .. 4 NT - 1: products of sixteen 4x4
+    // blocks with ones, lane l being column l % 4 of block l / 4, so that no
+    // lane's P meets another's (0 times a NaN of another row would be NaN).
+    // Measured in a prefill 32768 x 13 x 48: these 337 us, adds of the unpacked P
+    // 345.  (v_dot2_f32_bf16 holds up the matrix cores: four of them beside a
+    // 32x32x16 product take 29 ns, four v_fma_f32 17 ns.)
+    const s16x4_t ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
     auto sum_step = [&](const u32x4_t (&pk)[NT][2], int i) __attribute__((always_inline)) {
-        lsum[i % NT] = mfma_16x16x32(sel, as_bf16x8(pk[i % NT][i / NT]), lsum[i % NT]);
+        const int nt = i % NT, k = i / NT;
+        const u32x4_t x = pk[nt][k >> 1];
+        const u32x2_t h = (k & 1) ? u32x2_t{x.z, x.w} : u32x2_t{x.x, x.y};
+        lsum[nt] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(ones, __builtin_bit_cast(s16x4_t, h), lsum[nt], 0, 0, 0);
     };
     // visible keys of a lane's row within its unit: keys k0 + .. < lim
     auto row_limit = [&](const UnitInfo& ui, int nt) __attribute__((always_inline)) {
@@ -377,7 +379,7 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
                 const bool up = mt > m_ref[nt] + 8.f;
                 const float alpha = up ? fast_exp2(m_ref[nt] - mt) : 1.f;
                 m_ref[nt] = up ? mt : m_ref[nt];
-                lsum[nt] *= __shfl(alpha, (lane & 15) + 16 * hi);
+                lsum[nt] *= alpha;
 #pragma unroll
                 for (int dt = 0; dt < C::DT; ++dt) o[nt][dt] *= alpha;
             }
@@ -432,7 +434,8 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
             }
 #pragma unroll
             for (int j = i * 8 * NT / STEPS; j < (i + 1) * 8 * NT / STEPS; ++j) max_step(mx, sn, j);
-            if (i % (STEPS / (2 * NT)) == STEPS / (2 * NT) - 1) sum_step(pk, i / (STEPS / (2 * NT)));
+#pragma unroll
+            for (int j = i * 4 * NT / STEPS; j < (i + 1) * 4 * NT / STEPS; ++j) sum_step(pk, j);
         }
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+v"(mx[nt]));
@@ -530,7 +533,7 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
 #pragma unroll
             for (int i = 0; i < 2 * C::DT * NT; ++i) pv_step(pk, vf, i);
 #pragma unroll
-            for (int i = 0; i < 2 * NT; ++i) sum_step(pk, i);
+            for (int i = 0; i < 4 * NT; ++i) sum_step(pk, i);
         }
     }
     wait_vmcnt<0>();  // no DMA into the LDS outlives the work-group
@@ -538,8 +541,7 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
     if (!active) return;
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-        // tile row l % 32 of lsum, and past here this lane's row
-        const float l = __shfl(lsum[nt][0], (lane & 15) + 2 * (lane & 16));
+        const float l = lsum[nt][0] + __shfl_xor(lsum[nt][0], 32);  // both lanes of the row
         const int r = wrow0 + 32 * nt + l32;
         if (r >= nrows) continue;
         const long qr = row_qrow(a, vi, g, row0 + r);

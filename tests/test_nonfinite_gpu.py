@@ -32,6 +32,23 @@ def _same(a, b):
 
 
 @pytest.mark.parametrize("bad", VALUES)
+@pytest.mark.parametrize("E,N,L,H_q,H_kv,D", [(2, 40, 100, 7, 1, 128), (1, 2300, 0, 14, 2, 128), (24, 80, 700, 40, 8, 64)])
+def test_a_query_row_reaches_its_own_result_only(E, N, L, H_q, H_kv, D, bad):
+    q, kp, vp = _normal(1, (E, N, H_q, D)), _normal(2, (L, H_kv, D)), _normal(3, (L, H_kv, D), 0.5)
+    ke, ve, n, plen = _normal(4, (E, N, H_kv, D)), _normal(5, (E, N, H_kv, D), 0.5), dev_int([N] * E), dev_int([L])
+    out, lse = pdec.attn_prefill(q, kp, vp, ke, ve, n, plen)
+    q2 = q.clone()
+    hit = torch.zeros((E, N, H_q), dtype=torch.bool, device="cuda")
+    for e, j, h in ((0, 0, 0), (E - 1, N // 2, H_q - 1), (E // 2, N - 1, H_q // 2)):
+        hit[e, j, h] = True
+        q2[e, j, h, 5] = bad
+    out2, lse2 = pdec.attn_prefill(q2, kp, vp, ke, ve, n, plen)
+    torch.cuda.synchronize()
+    assert not torch.isfinite(out2[hit]).any()
+    assert _same(out[~hit], out2[~hit]) and _same(lse[~hit], lse2[~hit])
+
+
+@pytest.mark.parametrize("bad", VALUES)
 def test_a_row_gradient_reaches_only_key_units_it_may_see(bad):
     """dO of an early token is not finite: the cache rows of later 64-key units, which it does not see, keep their
     gradients (a 128-key tile walks the rows of both of its units)."""
