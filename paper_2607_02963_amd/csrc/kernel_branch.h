@@ -101,7 +101,7 @@ struct BranchCfg {
 
 // own_bound: a bound on the own units that one row group sees; rows_first: the
 // order in which work-groups take the items.
-template <int D, int NT, int NW>
+template <int D, int NT, int NW, bool CROSS>
 __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bound, int rows_first)
 {
     using C = BranchCfg<D, NT, NW>;
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
     // streams whose caches some row of the group sees, and their visible rows
     const int f_lo = row0 / per_stream, f_hi = (row0 + nrows - 1) / per_stream;
     const int tok_last = ((row0 + nrows - 1) / a.G) % a.qps;  // token of the group's last row
-    const int fa = a.cross ? 0 : f_lo, fb = a.cross ? vi.E - 1 : f_hi;
+    const int fa = CROSS ? 0 : f_lo, fb = CROSS ? vi.E - 1 : f_hi;
     const bool one = fa == fb;  // one stream: no table
     int own;                    // own units of the group
     int n_one = 0;
@@ -167,8 +167,8 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
             for (int f0 = fa; f0 <= fb; f0 += 64) {
                 const int f = f0 + lane;
                 // rows of stream f at or above the largest token that sees
-                // them are left out (a.cross: any row of the group may)
-                const int lim = f_lo < f_hi && (a.cross || f < f_hi) ? a.qps : tok_last + 1;
+                // them are left out (CROSS: any row of the group may)
+                const int lim = f_lo < f_hi && (CROSS || f < f_hi) ? a.qps : tok_last + 1;
                 const int n = f <= fb ? min(max(a.event_lens[vi.e0 + f], 0), lim) : 0;
                 const int units = (n + kUnit - 1) / kUnit;
                 int incl = units;
@@ -192,10 +192,6 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
     // the last slot takes whatever is left
     const int u1 = c_idx == nch - 1 ? upre + own : min(u0 + upc, upre + own);
     const int nst = __builtin_amdgcn_readfirstlane(max(0, u1 - u0));
-    // stages of the pipelined loop: all of them where every own unit belongs
-    // to the rows' one stream, else the prefix's (own units then concern few
-    // waves each, which the plain loop skips)
-    const int nd = one ? nst : min(max(upre - u0, 0), nst);
 
     auto unit = [&](int u) __attribute__((always_inline)) {
         const bool prefix = u < upre;
@@ -347,16 +343,16 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
     // visible keys of a lane's row within its unit: keys k0 + .. < lim
     auto row_limit = [&](const UnitInfo& ui, int nt) __attribute__((always_inline)) {
         const int seen = ui.stream < 0 || r_stream[nt] == ui.stream ? (ui.stream < 0 ? kUnit : r_tok[nt] + 1 - ui.k0)
-                                                                    : (a.cross ? r_tok[nt] - ui.k0 : 0);
+                                                                    : (CROSS ? r_tok[nt] - ui.k0 : 0);
         return min(ui.nk, seen);
+    };
+    auto mask_tile = [&](bf32x16_t& s, int lim) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = 8 * (i >> 2) + (i & 3) >= lim - 4 * hi ? kNegInf : s[i];
     };
     auto mask = [&](bf32x16_t (&s)[NT], int kb, const UnitInfo& ui) __attribute__((always_inline)) {
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const int lim = row_limit(ui, nt) - kb - 4 * hi;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) s[nt][i] = 8 * (i >> 2) + (i & 3) >= lim ? kNegInf : s[nt][i];
-        }
+        for (int nt = 0; nt < NT; ++nt) mask_tile(s[nt], row_limit(ui, nt) - kb);
     };
     // max of element pair i (0 .. 8 NT - 1) into mx
     auto max_step = [&](float (&mx)[NT], const bf32x16_t (&s)[NT], int i) __attribute__((always_inline)) {
@@ -367,22 +363,23 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
     // than 8 (every p is at most 2^8, and the final ratio is exact).  Each
     // lane tests its own keys; the max over the two lanes of a row is formed
     // only when some row moves.
+    auto rescale_tile = [&](float mx, int nt) __attribute__((always_inline)) {
+        const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+        const float mt = fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1])) * c;
+        const bool up = mt > m_ref[nt] + 8.f;
+        const float alpha = up ? fast_exp2(m_ref[nt] - mt) : 1.f;
+        m_ref[nt] = up ? mt : m_ref[nt];
+        lsum[nt] *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < C::DT; ++dt) o[nt][dt] *= alpha;
+    };
     auto rescale = [&](const float (&mx)[NT]) __attribute__((always_inline)) {
         bool need = false;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) need |= mx[nt] * c > m_ref[nt] + 8.f;
         if (__any(need)) {
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx[nt]), __float_as_uint(mx[nt]), false, false);
-                const float mt = fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1])) * c;
-                const bool up = mt > m_ref[nt] + 8.f;
-                const float alpha = up ? fast_exp2(m_ref[nt] - mt) : 1.f;
-                m_ref[nt] = up ? mt : m_ref[nt];
-                lsum[nt] *= alpha;
-#pragma unroll
-                for (int dt = 0; dt < C::DT; ++dt) o[nt][dt] *= alpha;
-            }
+            for (int nt = 0; nt < NT; ++nt) rescale_tile(mx[nt], nt);
         }
     };
     // P of element pair i (0 .. 8 NT - 1), rounded to bf16
@@ -441,79 +438,83 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
         for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+v"(mx[nt]));
     };
 
-    // ---- pipelined stages 0 .. nd - 1 ----
-    // Entering stage st: sa holds block 0's scores (masked, reference set),
-    // kf block 1's K operands, and stage st has landed for every wave.
+    // A masked key has p = 0, but 0 times an infinite or NaN value is NaN, so a
+    // unit's products may only meet rows that see some of it.  The pipelined
+    // loop takes the wave's first nd stages: the prefix's and, where every own
+    // unit belongs to the rows' one stream, those up to its first row's token,
+    // of which every row sees a part.  The plain loop takes the others, tile by
+    // tile and block by block, and keeps the rows that see nothing of a block as
+    // they were.
+    const int nd = !active ? 0 : min(max(upre + (one ? ((row0 + wrow0) / a.G) % a.qps / kUnit + 1 : 0) - u0, 0), nst);
+
+    // a unit that some row of this wave does not see whole
+    auto masked = [&](const UnitInfo& ui) __attribute__((always_inline)) {
+        bool m = ui.nk < kUnit;
+        if (ui.stream >= 0) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) m |= row_limit(ui, nt) < kUnit;
+        }
+        return __any(m) != 0;
+    };
+
+    // Every wave passes one barrier per stage; behind the one of stage st,
+    // stage st + 1 has landed and stage st - 1 been consumed for all of them, and
+    // the slot of the latter takes stage st + 3.
+    if (nst > 0) lds_barrier();  // the first three stages have landed
     if (nd > 0) {
-        stage_barrier<2 * C::PPW>();
-        if (!active) {
-            for (int st = 0; st < nd; ++st) {
-                stage_barrier<C::PPW>();
-                issue_stage(pending(st + 3));
-            }
-        } else {
-            bf32x16_t sa[NT], sb[NT];
-            u32x4_t kf[C::KS], pk[NT][2];
-            u32x2_t vf[4 * C::DT];
-            float mx[NT];
-            // a stage whose unit some row of this wave does not see whole
-            auto masked = [&](const UnitInfo& ui) __attribute__((always_inline)) {
-                bool m = ui.nk < kUnit;
-                if (ui.stream >= 0) {
+        // Entering stage st: sa holds block 0's scores (masked, reference set),
+        // kf block 1's K operands.
+        bf32x16_t sa[NT], sb[NT];
+        u32x4_t kf[C::KS], pk[NT][2];
+        u32x2_t vf[4 * C::DT];
+        float mx[NT];
+        UnitInfo ui = unit(u0);
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) m |= row_limit(ui, nt) < kUnit;
-                }
-                return __any(m) != 0;
-            };
-            UnitInfo ui = unit(u0);
+        for (int t = 0; t < C::KS; ++t) read_k(kf, slot(0), 0, t);
 #pragma unroll
-            for (int t = 0; t < C::KS; ++t) read_k(kf, slot(0), 0, t);
+        for (int i = 0; i < NT * C::KS; ++i) score_step(sa, kf, i);
+        bool msk = masked(ui);
+        if (msk) mask(sa, 0, ui);
 #pragma unroll
-            for (int i = 0; i < NT * C::KS; ++i) score_step(sa, kf, i);
-            bool msk = masked(ui);
-            if (msk) mask(sa, 0, ui);
+        for (int i = 0; i < 8 * NT; ++i) max_step(mx, sa, i);
+        rescale(mx);
 #pragma unroll
-            for (int i = 0; i < 8 * NT; ++i) max_step(mx, sa, i);
+        for (int t = 0; t < C::KS; ++t) read_k(kf, slot(0), 32, t);
+        for (int st = 0; st < nd; ++st) {
+            const unsigned char* buf = slot(st);
+            const unsigned char* nbuf = slot(st + 1);
+            phase_a(sb, sa, pk, kf, vf, buf, 0);
+            if (msk) mask(sb, 32, ui);
+            const Pending pd = pending(st + 3);
+            stage_barrier<C::PPW>();
+            phase_b(std::true_type{}, pk, vf, sb, mx, kf, nbuf, 0, pd);
             rescale(mx);
-#pragma unroll
-            for (int t = 0; t < C::KS; ++t) read_k(kf, slot(0), 32, t);
-            for (int st = 0; st < nd; ++st) {
-                const unsigned char* buf = slot(st);
-                const unsigned char* nbuf = slot(st + 1);
-                phase_a(sb, sa, pk, kf, vf, buf, 0);
-                if (msk) mask(sb, 32, ui);
-                // stage st + 1 has landed, and stage st - 1 been consumed, for
-                // every wave: its slot takes stage st + 3
-                const Pending pd = pending(st + 3);
-                stage_barrier<C::PPW>();
-                phase_b(std::true_type{}, pk, vf, sb, mx, kf, nbuf, 0, pd);
-                rescale(mx);
-                phase_a(sa, sb, pk, kf, vf, buf, 32);
-                const bool more = st + 1 < nd;
-                if (more) {
-                    ui = unit(u0 + st + 1);
-                    msk = masked(ui);
-                    if (msk) mask(sa, 0, ui);
-                }
-                phase_b(std::false_type{}, pk, vf, sa, mx, kf, nbuf, 32, pd);
-                if (more) rescale(mx);
+            phase_a(sa, sb, pk, kf, vf, buf, 32);
+            const bool more = st + 1 < nd;
+            if (more) {
+                ui = unit(u0 + st + 1);
+                msk = masked(ui);
+                if (msk) mask(sa, 0, ui);
             }
+            phase_b(std::false_type{}, pk, vf, sa, mx, kf, nbuf, 32, pd);
+            if (more) rescale(mx);
         }
     }
-
-    // ---- the other streams' units: each concerns the waves holding its rows ----
     for (int st = nd; st < nst; ++st) {
-        stage_barrier<2 * C::PPW>();
+        stage_barrier<C::PPW>();
         issue_stage(pending(st + 3));
-        const UnitInfo ui = unit(u0 + st);
-        int lim = 0;
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) lim = max(lim, row_limit(ui, nt));
-        if (!active || !__any(lim > 0)) continue;
         const unsigned char* buf = slot(st);
+        const UnitInfo ui = unit(u0 + st);
+        int lim[NT], most = 0;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            lim[nt] = row_limit(ui, nt);
+            most = max(most, lim[nt]);
+        }
+        if (!active) continue;
 #pragma unroll 1
         for (int kb = 0; kb < kUnit; kb += 32) {
-            if (!__any(lim > kb)) continue;
+            if (!__any(most > kb)) continue;
             u32x4_t kf[C::KS], pk[NT][2];
             u32x2_t vf[4 * C::DT];
             bf32x16_t s[NT];
@@ -522,18 +523,51 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
             for (int t = 0; t < C::KS; ++t) read_k(kf, buf, kb, t);
 #pragma unroll
             for (int j = 0; j < 4 * C::DT; ++j) read_v(vf, buf, kb, j);
+            // other streams' rows visible: both tiles at once, without the products
+            // of a tile that sees nothing
+            if constexpr (CROSS && NT > 1) {
 #pragma unroll
-            for (int i = 0; i < NT * C::KS; ++i) score_step(s, kf, i);
-            mask(s, kb, ui);
+                for (int i = 0; i < NT * C::KS; ++i) score_step(s, kf, i);
 #pragma unroll
-            for (int i = 0; i < 8 * NT; ++i) max_step(mx, s, i);
-            rescale(mx);
+                for (int nt = 0; nt < NT; ++nt) mask_tile(s[nt], lim[nt] - kb);
 #pragma unroll
-            for (int i = 0; i < 8 * NT; ++i) prob_step(pk, s, i);
+                for (int i = 0; i < 8 * NT; ++i) max_step(mx, s, i);
+                rescale(mx);
 #pragma unroll
-            for (int i = 0; i < 2 * C::DT * NT; ++i) pv_step(pk, vf, i);
+                for (int i = 0; i < 8 * NT; ++i) prob_step(pk, s, i);
 #pragma unroll
-            for (int i = 0; i < 4 * NT; ++i) sum_step(pk, i);
+                for (int i = 0; i < 4 * NT; ++i) sum_step(pk, i);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                    if (!__any(lim[nt] > kb)) continue;
+#pragma unroll
+                    for (int i = 0; i < 2 * C::DT; ++i) pv_step(pk, vf, i * NT + nt);
+                }
+                continue;
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const bool sees = lim[nt] > kb;
+                __builtin_amdgcn_sched_barrier(0);
+                if (!__any(sees)) continue;
+#pragma unroll
+                for (int t = 0; t < C::KS; ++t) score_step(s, kf, t * NT + nt);
+                mask_tile(s[nt], lim[nt] - kb);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) max_step(mx, s, 8 * nt + i);
+                if (__any(mx[nt] * c > m_ref[nt] + 8.f)) rescale_tile(mx[nt], nt);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) prob_step(pk, s, 8 * nt + i);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sum_step(pk, i * NT + nt);
+#pragma unroll
+                for (int dt = 0; dt < C::DT; ++dt) {
+                    bf32x16_t x = branch_mfma(v_op(vf, 0, dt), pk[nt][0], o[nt][dt]);
+                    x = branch_mfma(v_op(vf, 1, dt), pk[nt][1], x);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) o[nt][dt][i] = sees ? x[i] : o[nt][dt][i];
+                }
+            }
         }
     }
     wait_vmcnt<0>();  // no DMA into the LDS outlives the work-group

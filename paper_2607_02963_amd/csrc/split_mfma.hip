@@ -72,17 +72,28 @@ void launch_split_mfma(const StepArgs& a, int shape, int grid, hipStream_t strea
     }
 }
 
-// Whole branches: 64 rows per wave (two tiles) in groups of 256 rows, 32 in
-// groups of 128.
-void launch_branch(const StepArgs& a, int own_bound, bool rows_first, hipStream_t s)
+namespace {
+
+template <int D, bool CROSS>
+void launch_branch_rows(const StepArgs& a, int own_bound, bool rows_first, hipStream_t s)
 {
     const dim3 grid((unsigned)(8 * ((a.n_items + 7) / 8))), block(256);
+    if (a.rows_per_item == 256) hipLaunchKernelGGL((branch_kernel<D, 2, 4, CROSS>), grid, block, 0, s, a, own_bound, (int)rows_first);
+    else hipLaunchKernelGGL((branch_kernel<D, 1, 4, CROSS>), grid, block, 0, s, a, own_bound, (int)rows_first);
+}
+
+}  // namespace
+
+// Whole branches: 64 rows per wave (two tiles) in groups of 256 rows, 32 in
+// groups of 128.  The causal-attention variant has kernels of its own.
+void launch_branch(const StepArgs& a, int own_bound, bool rows_first, hipStream_t s)
+{
     if (a.D == 128) {
-        if (a.rows_per_item == 256) hipLaunchKernelGGL((branch_kernel<128, 2, 4>), grid, block, 0, s, a, own_bound, (int)rows_first);
-        else hipLaunchKernelGGL((branch_kernel<128, 1, 4>), grid, block, 0, s, a, own_bound, (int)rows_first);
+        if (a.cross) launch_branch_rows<128, true>(a, own_bound, rows_first, s);
+        else launch_branch_rows<128, false>(a, own_bound, rows_first, s);
     } else {
-        if (a.rows_per_item == 256) hipLaunchKernelGGL((branch_kernel<64, 2, 4>), grid, block, 0, s, a, own_bound, (int)rows_first);
-        else hipLaunchKernelGGL((branch_kernel<64, 1, 4>), grid, block, 0, s, a, own_bound, (int)rows_first);
+        if (a.cross) launch_branch_rows<64, true>(a, own_bound, rows_first, s);
+        else launch_branch_rows<64, false>(a, own_bound, rows_first, s);
     }
 }
 

@@ -32,6 +32,36 @@ def _same(a, b):
 
 
 @pytest.mark.parametrize("bad", VALUES)
+@pytest.mark.parametrize("E,N,L,H_q,H_kv,D,cross", [
+    (1, 200, 0, 1, 1, 128, 0),    # one stream, one head: a group spans several units
+    (1, 700, 70, 7, 1, 64, 0),
+    (1, 2300, 0, 14, 2, 128, 0),  # 256-row groups
+    (5, 13, 300, 28, 4, 128, 0),  # several streams in a group and in a wave
+    (9, 40, 130, 4, 1, 128, 1),   # the causal-attention variant
+    (3, 100, 4000, 40, 8, 64, 0),
+])
+def test_a_branch_value_reaches_only_rows_that_may_see_its_block(E, N, L, H_q, H_kv, D, cross, bad):
+    q, kp, vp = _normal(1, (E, N, H_q, D)), _normal(2, (L, H_kv, D)), _normal(3, (L, H_kv, D), 0.5)
+    ke, ve = _normal(4, (E, N, H_kv, D)), _normal(5, (E, N, H_kv, D), 0.5)
+    n, plen = dev_int([N] * E), dev_int([L])
+    call = lambda v: pdec.attn_prefill(q, kp, vp, ke, v, n, plen, cross=cross)  # noqa: E731
+    out, lse = call(ve)
+    e, t = E // 2, N - 2
+    ve2 = ve.clone()
+    ve2[e, t] = bad
+    out2, lse2 = call(ve2)
+    torch.cuda.synchronize()
+    assert torch.equal(lse, lse2)  # values have no part in it
+    assert not torch.isfinite(out2[e, t:]).any()
+    block = 32 * (t // 32)  # rows see a 32-key block whole or in part, or not at all
+    assert _same(out[e, :block], out2[e, :block])
+    for f in range(E):
+        if f != e:
+            upto = block if cross else N
+            assert _same(out[f, :upto], out2[f, :upto]), f
+
+
+@pytest.mark.parametrize("bad", VALUES)
 @pytest.mark.parametrize("E,N,L,H_q,H_kv,D", [(2, 40, 100, 7, 1, 128), (1, 2300, 0, 14, 2, 128), (24, 80, 700, 40, 8, 64)])
 def test_a_query_row_reaches_its_own_result_only(E, N, L, H_q, H_kv, D, bad):
     q, kp, vp = _normal(1, (E, N, H_q, D)), _normal(2, (L, H_kv, D)), _normal(3, (L, H_kv, D), 0.5)
