@@ -438,14 +438,42 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
         for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+v"(mx[nt]));
     };
 
+    // B where no row of the wave sees the block (other streams' rows visible):
+    // no products.
+    auto phase_b_idle = [&](auto dma, const bf32x16_t (&sn)[NT], float (&mx)[NT], u32x4_t (&kf)[C::KS],
+                            const unsigned char* nbuf, int nkb, const Pending& pd) __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < C::KS; ++t) read_k(kf, nbuf, nkb, t);
+        if constexpr (decltype(dma)::value) issue_stage(pd);
+#pragma unroll
+        for (int i = 0; i < 8 * NT; ++i) max_step(mx, sn, i);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) asm volatile("" : "+v"(mx[nt]));
+    };
+
     // A masked key has p = 0, but 0 times an infinite or NaN value is NaN, so a
     // unit's products may only meet rows that see some of it.  The pipelined
     // loop takes the wave's first nd stages: the prefix's and, where every own
     // unit belongs to the rows' one stream, those up to its first row's token,
     // of which every row sees a part.  The plain loop takes the others, tile by
     // tile and block by block, and keeps the rows that see nothing of a block as
-    // they were.
-    const int nd = !active ? 0 : min(max(upre + (one ? ((row0 + wrow0) / a.G) % a.qps / kUnit + 1 : 0) - u0, 0), nst);
+    // they were.  With other streams' rows visible nearly every row of a wave
+    // sees some of nearly every unit: the one-tile form takes them all in the
+    // pipelined loop, without products where its tile sees nothing of a block,
+    // and the plain loop leaves out tiles only.  (Videos of at most 64 rows, most
+    // of which are one tile, keep rows apart; branches of one block stay in the
+    // plain loop, which skips the unit's second one.)
+    const bool others = CROSS && NT == 1 && !one && R > 64 && a.qps > 32;
+    const int nd = !active ? 0
+                   : others ? nst
+                            : min(max(upre + (one ? ((row0 + wrow0) / a.G) % a.qps / kUnit + 1 : 0) - u0, 0), nst);
+    // bit b: some row of the wave sees some of block b of the unit
+    auto sees_blocks = [&](const UnitInfo& ui) __attribute__((always_inline)) {
+        if (!others || ui.stream < 0) return 3;
+        const int lim = row_limit(ui, 0);
+        return (__any(lim > 0) ? 1 : 0) | (__any(lim > 32) ? 2 : 0);
+    };
 
     // a unit that some row of this wave does not see whole
     auto masked = [&](const UnitInfo& ui) __attribute__((always_inline)) {
@@ -474,6 +502,7 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
 #pragma unroll
         for (int i = 0; i < NT * C::KS; ++i) score_step(sa, kf, i);
         bool msk = masked(ui);
+        int sees = sees_blocks(ui);
         if (msk) mask(sa, 0, ui);
 #pragma unroll
         for (int i = 0; i < 8 * NT; ++i) max_step(mx, sa, i);
@@ -487,16 +516,20 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
             if (msk) mask(sb, 32, ui);
             const Pending pd = pending(st + 3);
             stage_barrier<C::PPW>();
-            phase_b(std::true_type{}, pk, vf, sb, mx, kf, nbuf, 0, pd);
+            if (sees & 1) phase_b(std::true_type{}, pk, vf, sb, mx, kf, nbuf, 0, pd);
+            else phase_b_idle(std::true_type{}, sb, mx, kf, nbuf, 0, pd);
             rescale(mx);
             phase_a(sa, sb, pk, kf, vf, buf, 32);
             const bool more = st + 1 < nd;
+            const int saw = sees;
             if (more) {
                 ui = unit(u0 + st + 1);
                 msk = masked(ui);
+                sees = sees_blocks(ui);
                 if (msk) mask(sa, 0, ui);
             }
-            phase_b(std::false_type{}, pk, vf, sa, mx, kf, nbuf, 32, pd);
+            if (saw & 2) phase_b(std::false_type{}, pk, vf, sa, mx, kf, nbuf, 32, pd);
+            else phase_b_idle(std::false_type{}, sa, mx, kf, nbuf, 32, pd);
             if (more) rescale(mx);
         }
     }
@@ -525,7 +558,7 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
             for (int j = 0; j < 4 * C::DT; ++j) read_v(vf, buf, kb, j);
             // other streams' rows visible: both tiles at once, without the products
             // of a tile that sees nothing
-            if constexpr (CROSS && NT > 1) {
+            if (CROSS && (NT > 1 || R > 64)) {
 #pragma unroll
                 for (int i = 0; i < NT * C::KS; ++i) score_step(s, kf, i);
 #pragma unroll

@@ -192,7 +192,11 @@ Plan make_branch_plan(const pdec_dims* d, int num_videos)
             own = spans >= 2 ? (spans - 1) * full + std::min(full, ceil_div(rt / G + 2, kUnitKeys)) : full;
         }
         const long units = std::max<long>(upre + own, 1);
-        const bool rows_first = num_videos > 1 || own > upre;
+        // the row groups of a causal sequence differ in length; with other streams'
+        // rows visible those of short branches do not, and take whole rounds (13 x
+        // 100 tokens over 400 keys: 264 items 67 us, 176 items 45; 2 x 700 over
+        // none: 35 us and 40)
+        const bool rows_first = num_videos > 1 || (own > upre && (!d->cross_causal || full > 3));
         // a stream's rows see half of its units on average
         const double mean_units = (double)tokens / num_videos / kUnitKeys + (d->cross_causal ? own : 0.5 * own);
         const double unit_us = rt == 256 ? 2.1 : 1.3, fixed_units = 4.0;

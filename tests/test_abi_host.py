@@ -348,3 +348,12 @@ def test_whole_branch_plan_stays_within_the_static_scratch_unless_it_has_one_slo
     assert info["row_groups"] == -(-E * N * (H_q // H_kv) // info["rows_per_item"])
     units = -(-L // 64) + (1 if E > 1 else -(-N // 64))
     assert info["max_chunks"] * info["chunk_keys"] >= 64 * units
+
+
+@pytest.mark.parametrize("E,N,L,H", [(13, 100, 400, 8), (24, 64, 100, 4)])
+def test_equal_row_groups_of_the_causal_attention_variant_are_planned_in_whole_rounds(E, N, L, H):
+    """With other streams' rows visible a short branch's row groups are as long
+    as each other: a second round of a few items would double the call."""
+    d = pdec.make_dims(E, H, H, 128, N, L, pdec.PDEC_DTYPE_BF16, queries_per_stream=N, cross_causal=1)
+    items = pdec.describe_plan(d)["work_items"]
+    assert items <= 256 or items % 256 > 128, items

@@ -27,6 +27,8 @@ CASES = [
     (5, 13, 1983, [13, 0, 7, 13, 1], 14, 2, 128, 16, 0),  # several chunks, a partial last prefix unit
     (9, 40, 130, [40, 64, 3, 40, 0, 40, 39, 33, 32], 4, 1, 128, 64, 1),  # other streams' units, lengths above N
     (70, 2, 200, [2] * 69 + [0], 2, 2, 64, 2, 1),         # more streams than one scan of the unit table
+    (5, 100, 70, [100, 64, 0, 65, 3], 4, 1, 128, 100, 1), # other streams' second units, which some waves see nothing of
+    (3, 150, 0, [150, 129, 128], 6, 2, 64, 150, 1),
     (40, 8, 6000, [8] * 40, 28, 4, 128, 8, 0),            # few-slot rows
     (2, 3, 9000, [3, 3], 2, 1, 128, 3, 0),                # many slots per row
 ]
