@@ -125,7 +125,13 @@ __global__ __launch_bounds__(256, 2) void split_f32_kernel(StepArgs a)
         for (int dt = 0; dt < DT; ++dt) o[nt][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
 
-    while (u < it.u1) {
+    // Units of which a row may see nothing, streams' own and those of the plan
+    // segment under the self-only mask, come last.  There a row that sees none of
+    // the wave's keys keeps its sums as they are: 0 times an infinite or NaN
+    // value of another stream would be NaN.
+    auto apart_unit = [&](const UnitInfo& x) { return x.stream >= 0 || (PLAN && x.k0 + kUnit > it.vi.plan0); };
+    auto unit_pass = [&](auto apart) __attribute__((always_inline)) {
+        constexpr bool APART = decltype(apart)::value;
         const UnitInfo cur = ui;
         f32x4_t s[NT][2];  // two sums per tile: the products of one wait for each other
 #pragma unroll
@@ -139,21 +145,32 @@ __global__ __launch_bounds__(256, 2) void split_f32_kernel(StepArgs a)
         if (u < it.u1) load_k(ui);  // in flight under this unit's softmax and P V
 
         if (16 * w < cur.nk) {
-            const bool plan_unit = PLAN && cur.stream < 0 && cur.k0 + kUnit > it.vi.plan0;  // self-only mask
+            const bool plan_unit = PLAN && APART && cur.stream < 0;  // self-only mask
+            bool none[NT];
             float p[NT][4], mx[NT];
             bool need = false;
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                const bool row_sees = row_stream[nt] != -2 && (cur.stream < 0 || row_stream[nt] == cur.stream);
+                const bool row_sees =
+                    row_stream[nt] != -2 && (!APART || cur.stream < 0 || row_stream[nt] == cur.stream);
+                bool sees[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int key = 16 * w + 4 * lg + i;
-                    bool see = row_sees & (key < cur.nk);
-                    if (plan_unit) see = see & !plan_key_hidden(a, it.vi, cur.k0 + key, row_stream[nt]);
-                    p[nt][i] = see ? (s[nt][0][i] + s[nt][1][i]) * c : kNegInf;
+                    sees[i] = row_sees & (key < cur.nk);
+                    if (plan_unit) sees[i] = sees[i] & !plan_key_hidden(a, it.vi, cur.k0 + key, row_stream[nt]);
+                    p[nt][i] = sees[i] ? (s[nt][0][i] + s[nt][1][i]) * c : kNegInf;
                 }
                 mx[nt] = fmaxf(fmaxf(p[nt][0], p[nt][1]), fmaxf(p[nt][2], p[nt][3]));
                 need |= mx[nt] > m_ref[nt] + 8.f;
+                none[nt] = !row_sees;
+                if (plan_unit) {  // some lane of the row (one of four) sees a key
+                    uint64_t b = 0;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) b |= __ballot(sees[i]);
+                    b |= b >> 32;
+                    none[nt] = ((b | (b >> 16)) >> l16 & 1) == 0;
+                }
             }
             if (__any(need)) {  // rare after a row's first keys
 #pragma unroll
@@ -174,16 +191,33 @@ __global__ __launch_bounds__(256, 2) void split_f32_kernel(StepArgs a)
                     p[nt][i] = fast_exp2(p[nt][i] - m_ref[nt]);  // 0 for a hidden key
                     l_lane[nt] += p[nt][i];
                 }
+            if constexpr (!APART) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt)
+                    for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        o[nt][dt] = mfma_16x16x4(vx[i][dt >> 2][dt & 3], p[nt][i], o[nt][dt]);
+                        for (int nt = 0; nt < NT; ++nt)
+                            o[nt][dt] = mfma_16x16x4(vx[i][dt >> 2][dt & 3], p[nt][i], o[nt][dt]);
+            } else {
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) {
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        f32x4_t x = o[nt][dt];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) x = mfma_16x16x4(vx[i][dt >> 2][dt & 3], p[nt][i], x);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) o[nt][dt][j] = none[nt] ? o[nt][dt][j] : x[j];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);  // one d tile at a time: few registers
+                }
+            }
         }
         if (u < it.u1) load_v(ui);  // under the next scores
-    }
+    };
+    while (u < it.u1 && !apart_unit(ui)) unit_pass(std::false_type{});
+    while (u < it.u1) unit_pass(std::true_type{});
 
     // ---- merge of the four waves, and the item's slot ----
     // lane: row l % 16 of tile nt, d = D/4 (l / 16) + DT j + dt

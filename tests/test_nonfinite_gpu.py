@@ -79,6 +79,31 @@ def test_a_query_row_reaches_its_own_result_only(E, N, L, H_q, H_kv, D, bad):
 
 
 @pytest.mark.parametrize("bad", VALUES)
+@pytest.mark.parametrize("E,L,H_q,H_kv,D,plan", [(8, 300, 4, 1, 128, 0), (5, 130, 28, 4, 64, 0), (48, 8000, 4, 2, 128, 0),
+                                                  (8, 256, 4, 1, 128, 16)])
+def test_a_float32_stream_value_reaches_its_own_rows_only(E, L, H_q, H_kv, D, plan, bad):
+    f32 = torch.float32
+    q, kp, vp = _normal(1, (E, H_q, D), 1.0, f32), _normal(2, (L, H_kv, D), 1.0, f32), _normal(3, (L, H_kv, D), 0.5, f32)
+    ke, ve = _normal(4, (E, 20, H_kv, D), 1.0, f32), _normal(5, (E, 20, H_kv, D), 0.5, f32)
+    n, plen = dev_int([9 + e % 11 for e in range(E)]), dev_int([L])
+    call = lambda v, p: pdec.attn_step(q, kp, p, ke, v, n, plen, plan_mask=int(plan > 0), plan_per_stream=plan)  # noqa: E731
+    out, lse = call(ve, vp)
+    e = E // 2
+    ve2, vp2 = ve.clone(), vp.clone()
+    if plan:
+        vp2[L - E * plan + e * plan + 3] = bad  # one of stream e's own plan tokens
+    else:
+        ve2[e, 4] = bad
+    out2, lse2 = call(ve2, vp2)
+    torch.cuda.synchronize()
+    assert torch.equal(lse, lse2)
+    assert not torch.isfinite(out2[e]).any()
+    for f in range(E):
+        if f != e:
+            assert _same(out[f], out2[f]), f
+
+
+@pytest.mark.parametrize("bad", VALUES)
 def test_a_row_gradient_reaches_only_key_units_it_may_see(bad):
     """dO of an early token is not finite: the cache rows of later 64-key units, which it does not see, keep their
     gradients (a 128-key tile walks the rows of both of its units)."""
