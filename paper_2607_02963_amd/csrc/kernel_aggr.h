@@ -87,10 +87,19 @@ __device__ inline void add8(float* acc, const float4* p)
     acc[7] += p[1].w;
 }
 
+// A 16-byte load of an input that passes through once: STREAM leaves the caches
+// to what is read again.
+template <bool STREAM>
+__device__ inline u32x4_t aggr_load(const u32x4_t* p)
+{
+    if constexpr (STREAM) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
 // ---- pass 1: head-averaged attention weights of the chunk's 64 tokens ----
 // Writes wl[j] = w of token 64c + j (0 past N), and the caller's weights
 // output when there is one.
-template <int D>
+template <int D, bool STREAM>
 __device__ inline void aggr_chunk_weights(const AggrArgs& a, int c, float* wl, float (*wpart)[kAggrChunk])
 {
     constexpr int KSTEPS = D / 32;
@@ -108,7 +117,7 @@ __device__ inline void aggr_chunk_weights(const AggrArgs& a, int c, float* wl, f
             const uint16_t* row = a.k + ((long)min(tok, a.N - 1) * a.H_kv + gk) * D;
 #pragma unroll
             for (int t = 0; t < KSTEPS; ++t) {
-                kb[tt][t] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(row + 32 * t + 8 * lg));
+                kb[tt][t] = aggr_load<STREAM>(reinterpret_cast<const u32x4_t*>(row + 32 * t + 8 * lg));
                 if (tok >= a.N) kb[tt][t] = u32x4_t{0u, 0u, 0u, 0u};
             }
         }
@@ -161,15 +170,13 @@ __device__ inline void aggr_chunk_weights(const AggrArgs& a, int c, float* wl, f
 }
 
 // ---- pass 2: weighted sums of embedding rows per segment piece ----
-// Bound by HBM: embeddings and keys pass through once, so their loads are
-// nontemporal and leave the caches to the pieces, which pass 3 reads back
-// (32704 tokens x 3584, 268 MB: a call 62.9 us with ordinary loads, 55.9 with
-// these, 4.8 TB/s; a large copy moves 4.76.  Tokens that are in the caches
-// already, 1000 to 32704 of them: none slower).
+// Bound by HBM: embeddings and keys pass through once.  STREAM reads them past
+// the caches, which keep the pieces that pass 3 reads back (32704 tokens x 3584
+// with their keys, 268 MB: a call 62.9 -> 55.9 us).
 // Thread tid covers the 8-element vectors tid + 256 r, r < R, of a row.  DA
 // is the head width in attention mode (the weights come from pass 1, done
 // here first), 0 in the other modes.
-template <int R, int DA>
+template <int R, int DA, bool STREAM>
 __global__ __launch_bounds__(256) void aggr_pool_kernel(AggrArgs a)
 {
     constexpr int U = 8;  // rows loaded ahead
@@ -178,7 +185,7 @@ __global__ __launch_bounds__(256) void aggr_pool_kernel(AggrArgs a)
     const int tid = threadIdx.x;
     const int V8 = a.hidden / 8;
     const int c = blockIdx.x;
-    if constexpr (DA > 0) aggr_chunk_weights<DA>(a, c, wl, wpart);
+    if constexpr (DA > 0) aggr_chunk_weights<DA, STREAM>(a, c, wl, wpart);
     const int lo = min(max(a.cu_seg[0], 0), a.N);
     const int hi = min(max(a.cu_seg[a.S], lo), a.N);
     const int t0 = max(c * kAggrChunk, lo);
@@ -235,7 +242,7 @@ __global__ __launch_bounds__(256) void aggr_pool_kernel(AggrArgs a)
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int v = tid + 256 * r;
-                xv[u][r] = v < V8 ? __builtin_nontemporal_load(row + v) : u32x4_t{0u, 0u, 0u, 0u};
+                xv[u][r] = v < V8 ? aggr_load<STREAM>(row + v) : u32x4_t{0u, 0u, 0u, 0u};
             }
             if constexpr (DA > 0) wv[u] = wl[t - c * kAggrChunk];
             else wv[u] = a.mode == kAggrModeUniform ? 1.f : a.scores[t];

@@ -168,3 +168,31 @@ def test_aggregation_many_salient_segments(S, hidden):
     w.salient[19, :] = 1
     for mode in ("learned", "attention"):
         _check(w, mode)
+
+
+@pytest.mark.parametrize("mode", ["uniform", "learned", "attention"])
+def test_aggregation_of_inputs_larger_than_the_caches(mode):
+    """33000 tokens x 4096 (270 MB) take the loads that pass the caches by; their sums are the ordinary ones, so the
+    result is bit for bit that of each event's tokens alone, a call below the line, for events of one segment."""
+    N, S, K, h, H_q, H_kv, D = 33000, 64, 8, 4096, 8, 2, 64
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    r = lambda *s: torch.randn(s, generator=gen, device="cuda").bfloat16()  # noqa: E731
+    g, x = r(K, h), r(N, h)
+    cuts = [0] + [64 * (8 * i + i % 3) + 5 * (i % 2) for i in range(1, S)] + [N]
+    sal = torch.zeros((K, S), dtype=torch.uint8)
+    picks = [0, 1, 9, 20, 33, 41, 62, 63]
+    for i, s in enumerate(picks):
+        sal[i, s] = 1
+    kw = {}
+    if mode == "learned":
+        kw["scores"] = torch.rand(N, generator=gen, device="cuda") + 0.1
+    if mode == "attention":
+        kw = dict(q=r(H_q, D), k=r(N, H_kv, D), lse=torch.full((H_q,), 11.0, device="cuda"))
+    out = pdec.aggregate(g, x, dev_int(cuts), sal.cuda(), mode, **kw)
+    for i, s in enumerate(picks):
+        a, b = cuts[s] // 64 * 64, cuts[s + 1]  # from the start of the segment's first 64-token chunk
+        part = {k: v[a:b] if k in ("scores", "k") else v for k, v in kw.items()}
+        one = pdec.aggregate(g[i:i + 1], x[a:b].contiguous(), dev_int([0, cuts[s] - a, b - a]),
+                             torch.tensor([[0, 1]], dtype=torch.uint8).cuda(), mode, **part)
+        torch.cuda.synchronize()
+        assert torch.equal(one[0], out[i]), (mode, i)
