@@ -112,36 +112,78 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
     __shared__ int tab_nlen[kMaxStreamsPerVideo];
 
     // ---- which item; every branch is uniform over the work-group ----
-    // Row groups of one chunk read the same keys.  A single video's items are
-    // cut into eight contiguous runs, one per XCD (block b runs on XCD b % 8),
-    // so that they meet in one L2 and every XCD gets as many.  Where chunks
-    // or row groups differ in length (a batch, a causal sequence) the blocks
-    // take the (chunk, video, head) triples in turn instead, the longest row
-    // groups first, so that the long items are spread over the XCDs.
-    const int P = a.n_items / a.rg_max;  // (chunk, video, head) triples
-    int p, rg;
-    if (rows_first) {
-        const int b = wg_id();
-        if (b >= a.n_items) return;
-        p = b % P;
-        rg = a.rg_max - 1 - b / P;
+    // Row groups of one chunk read the same keys.  They are numbered one after
+    // another and the items cut into eight contiguous runs, one per XCD (block b
+    // runs on XCD b % 8), so that they meet in one L2 and every XCD gets as many.
+    // The items of a causal sequence, whose row groups differ in length, are taken
+    // in another order instead: the (chunk, head) pairs in turn, the longest row
+    // groups first, so that the long items are spread over the XCDs.  A batch's
+    // videos differ in their numbers of row groups and chunks: there the items
+    // that exist are counted first.
+    const int upc = a.unit_per_chunk;
+    auto chunks_of = [&](const VideoInfo& x) __attribute__((always_inline)) {  // slots that hold states
+        return min(max(((x.L + kUnit - 1) / kUnit + own_bound + upc - 1) / upc, 1), a.max_chunks);
+    };
+    int v = 0, c_idx, g, rg;
+    if (a.num_videos > 1) {
+        const int l = wi_id() & 63;
+        auto items_of = [&](int x) __attribute__((always_inline)) {
+            if (x >= a.num_videos) return 0;
+            const VideoInfo xi = video_info(a, x);
+            return a.H_kv * chunks_of(xi) * ((xi.E * a.G * a.qps + C::RT - 1) / C::RT);
+        };
+        auto scan = [&](int x) __attribute__((always_inline)) {  // inclusive, over the lanes
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const int y = __shfl_up(x, off);
+                if (l >= off) x += y;
+            }
+            return x;
+        };
+        int total = 0;
+        for (int v0 = 0; v0 < a.num_videos; v0 += 64) total += __shfl(scan(items_of(v0 + l)), 63);
+        const int per = (total + 7) / 8;
+        int i = (wg_id() % 8) * per + wg_id() / 8;
+        if (wg_id() / 8 >= per || i >= total) return;
+        for (int v0 = 0;; v0 += 64) {
+            const int n = items_of(v0 + l), incl = scan(n), all = __shfl(incl, 63);
+            if (i >= all) {
+                i -= all;
+                continue;
+            }
+            const int at = __builtin_ctzll(__ballot(incl > i));
+            v = v0 + at;
+            i -= __shfl(incl - n, at);
+            break;
+        }
+        v = __builtin_amdgcn_readfirstlane(v);
+        i = __builtin_amdgcn_readfirstlane(i);
+        const int groups = (video_info(a, v).E * a.G * a.qps + C::RT - 1) / C::RT;
+        rg = i % groups;
+        g = i / groups % a.H_kv;
+        c_idx = i / groups / a.H_kv;
     } else {
-        const int per = (a.n_items + 7) / 8;
-        const int i = (wg_id() % 8) * per + wg_id() / 8;
-        if (i >= a.n_items || wg_id() / 8 >= per) return;
-        p = i / a.rg_max;
-        rg = i % a.rg_max;
+        const int b = wg_id(), P = a.n_items / a.rg_max, per = (a.n_items + 7) / 8;
+        int p;
+        if (rows_first) {
+            if (b >= a.n_items) return;
+            p = b % P;
+            rg = a.rg_max - 1 - b / P;
+        } else {
+            const int i = (b % 8) * per + b / 8;
+            if (i >= a.n_items || b / 8 >= per) return;
+            p = i / a.rg_max;
+            rg = i % a.rg_max;
+        }
+        g = p % a.H_kv;
+        c_idx = p / a.H_kv;
     }
-    const int g = p % a.H_kv;
-    const int v = (p / a.H_kv) % a.num_videos;
-    const int c_idx = p / (a.H_kv * a.num_videos);
     const VideoInfo vi = video_info(a, v);
     const int per_stream = a.G * a.qps;
     const int R = vi.E * per_stream;
     const int row0 = rg * C::RT;
     const int upre = (vi.L + kUnit - 1) / kUnit;
-    const int upc = a.unit_per_chunk;
-    const int nch = min(max((upre + own_bound + upc - 1) / upc, 1), a.max_chunks);  // slots that hold states
+    const int nch = chunks_of(vi);
     if (c_idx == 0 && g == 0 && rg == 0 && wi_id() == 0) a.video_chunks[v] = nch;
     if (row0 >= R || c_idx >= nch) return;
     const int nrows = min(C::RT, R - row0);

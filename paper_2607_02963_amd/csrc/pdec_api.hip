@@ -167,9 +167,9 @@ void size_workspace(const pdec_dims* d, int num_videos, Plan* p)
 // and chunk count are the pair with the least estimated time: the rounds its
 // items take on the compute units, each an item's units plus a fixed cost, and
 // the finish pass over the slots.  A unit takes about 2.1 us at 256 rows (the
-// 16384-token causal prefill) and a little over half of that at 128, whose
-// waves read the LDS twice as often per row: 256 rows serve the long cases,
-// 128 those with too few items to fill the chip.
+// 16384-token causal prefill; 1.9 at D = 64) and a little over half of that at
+// 128 (1.2), whose waves read the LDS twice as often per row: 256 rows serve
+// the long cases, 128 those with too few items to fill the chip.
 Plan make_branch_plan(const pdec_dims* d, int num_videos)
 {
     const int G = d->num_q_heads / d->num_kv_heads;
@@ -193,21 +193,29 @@ Plan make_branch_plan(const pdec_dims* d, int num_videos)
         }
         const long units = std::max<long>(upre + own, 1);
         // the row groups of a causal sequence differ in length; with other streams'
-        // rows visible those of short branches do not, and take whole rounds (13 x
-        // 100 tokens over 400 keys: 264 items 67 us, 176 items 45; 2 x 700 over
-        // none: 35 us and 40)
-        const bool rows_first = num_videos > 1 || (own > upre && (!d->cross_causal || full > 3));
+        // rows visible those of short branches do not, and take whole rounds, as
+        // those of prefixes do (13 x 100 tokens over 400 keys: 264 items 67 us, 176
+        // items 45; 2 x 700 over none: 35 us and 40)
+        const bool rows_first = own > upre && (!d->cross_causal || full > 3);
         // a stream's rows see half of its units on average
         const double mean_units = (double)tokens / num_videos / kUnitKeys + (d->cross_causal ? own : 0.5 * own);
         const double unit_us = rt == 256 ? 2.1 : 1.3, fixed_units = 4.0;
+        // row groups and units of a batch's videos, which are below their bounds
+        const double rg_mean = (double)d->num_events * per / num_videos / rt;
+        const double filled = (double)tokens / num_videos / kUnitKeys + own;
         for (long n = 1; n <= std::min<long>(units, kMaxChunks); ++n) {
             // no more states than the scratch of pdec_attn_step_noalloc holds
             if (n > 1 && n * rows * slot_bytes + num_videos * 4.0 > (double)PDEC_NOALLOC_SCRATCH_BYTES) break;
             const long upc = ceil_div(units, n);
             if (ceil_div(units, upc) != n) continue;  // fewer chunks of the same length do
-            const double items = (double)num_videos * d->num_kv_heads * rg * n;
+            // Items that exist: in a batch every video rounds both up, by half on
+            // average (and by more than that in one batch of two: 6% are added, as
+            // a second round of a few items costs as much as the first).
+            const double items = num_videos == 1 ? (double)d->num_kv_heads * rg * n
+                                                 : 1.06 * num_videos * d->num_kv_heads * std::min<double>(rg, std::max(1.0, rg_mean + 0.5)) *
+                                                       std::min<double>(n, filled / upc + 0.5);
             double t = rows_first ? std::max(upc + fixed_units, items * (mean_units / n + fixed_units) / kTargetItems)
-                                  : std::ceil(items / kTargetItems) * (upc + fixed_units);
+                              : std::ceil(items / kTargetItems) * (upc + fixed_units);
             t *= unit_us;
             if (n > 1) t += 4.0 + rows * n * slot_bytes / 4.0e6;
             if (best >= 0.0 && t >= best) continue;

@@ -357,3 +357,13 @@ def test_equal_row_groups_of_the_causal_attention_variant_are_planned_in_whole_r
     d = pdec.make_dims(E, H, H, 128, N, L, pdec.PDEC_DTYPE_BF16, queries_per_stream=N, cross_causal=1)
     items = pdec.describe_plan(d)["work_items"]
     assert items <= 256 or items % 256 > 128, items
+
+
+def test_a_batch_of_unequal_videos_is_cut_for_the_items_that_exist():
+    """13 streams and 2: the bound on the streams of a video says 26, and cutting
+    for those left half of the chip idle."""
+    d = pdec.make_dims(15, 28, 4, 64, 6, 11448, pdec.PDEC_DTYPE_BF16, max_events_per_video=13, prefix_tokens=21866,
+                       queries_per_stream=6)
+    info = pdec.describe_plan(d, 2)
+    groups = sum(-(-e * 6 * 7 // info["rows_per_item"]) for e in (13, 2))
+    assert 192 <= groups * 4 * info["max_chunks"] <= 256, info

@@ -67,3 +67,28 @@ def test_branch_prefix_shorter_than_its_bound():
     ref_o, ref_l = oracle.attn_prefill(q, kp[:L], vp[:L], ke, ve, n, [0, L], [0, E])
     check("bf16", host(out).reshape(E * N, H_q, D), host(lse).reshape(E * N, H_q), ref_o.reshape(E * N, H_q, D),
           ref_l.reshape(E * N, H_q), what="branch short prefix")
+
+
+@pytest.mark.parametrize("V,cross", [(2, 0), (5, 1), (70, 0)])
+def test_branch_batch_of_unequal_videos(V, cross):
+    """Videos without streams, without a prefix, with one row group and with
+    several: the items that exist are numbered over the videos, 64 of them at a
+    time."""
+    rng = np.random.default_rng(40 + V)
+    N, H_q, H_kv, D = 21, 14, 2, 128
+    events = [13, 1] if V == 2 else rng.integers(0, 4, V).tolist()
+    events[-1] = max(events[-1], 1)
+    prefix = [1500, 900] if V == 2 else (rng.integers(0, 5, V) * 67).tolist()
+    SE, SL = sum(events), sum(prefix)
+    f = lambda s, *shape: wl.bf16_bits((s * rng.standard_normal(shape)).astype(np.float32))  # noqa: E731
+    q, kp, vp = f(1.5, SE, N, H_q, D), f(1.0, SL, H_kv, D), f(0.5, SL, H_kv, D)
+    ke, ve = f(1.0, SE, N, H_kv, D), f(0.5, SE, N, H_kv, D)
+    n = rng.integers(0, N + 1, SE).astype(np.int32)
+    cup, cue = np.concatenate([[0], np.cumsum(prefix)]), np.concatenate([[0], np.cumsum(events)])
+    out, lse = pdec.attn_prefill_ragged(dev_float(q, "bf16"), dev_float(kp, "bf16"), dev_float(vp, "bf16"), dev_int(cup),
+                                        dev_float(ke, "bf16"), dev_float(ve, "bf16"), dev_int(n), dev_int(cue),
+                                        max_prefix_len=max(prefix), max_events_per_video=max(events), cross=cross)
+    torch.cuda.synchronize()
+    ref_o, ref_l = oracle.attn_prefill(q, kp, vp, ke, ve, n, cup.astype(np.int32), cue.astype(np.int32), cross=cross)
+    check("bf16", host(out).reshape(SE * N, H_q, D), host(lse).reshape(SE * N, H_q), ref_o.reshape(SE * N, H_q, D),
+          ref_l.reshape(SE * N, H_q), what=f"branch batch {V}")
