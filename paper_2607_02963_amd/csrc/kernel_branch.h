@@ -167,8 +167,11 @@ __global__ __launch_bounds__(64 * NW) void branch_kernel(StepArgs a, int own_bou
         int p;
         if (rows_first) {
             if (b >= a.n_items) return;
-            p = b % P;
-            rg = a.rg_max - 1 - b / P;
+            // where the eight XCDs would each meet the same pairs in every step, the
+            // chunks move on by one, so that each gets early ones and late, short ones
+            const int step = b / P;
+            p = (b % P + a.H_kv * (P % 8 == 0 ? step : 8 % P == 0 ? step * P / 8 : 0)) % P;
+            rg = a.rg_max - 1 - step;
         } else {
             const int i = (b % 8) * per + b / 8;
             if (i >= a.n_items || b / 8 >= per) return;

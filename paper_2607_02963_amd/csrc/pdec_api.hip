@@ -199,7 +199,9 @@ Plan make_branch_plan(const pdec_dims* d, int num_videos)
         const bool rows_first = own > upre && (!d->cross_causal || full > 3);
         // a stream's rows see half of its units on average
         const double mean_units = (double)tokens / num_videos / kUnitKeys + (d->cross_causal ? own : 0.5 * own);
-        const double unit_us = rt == 256 ? 2.1 : 1.3, fixed_units = 4.0;
+        // (other streams' units, most of them masked, take longer: 2.4 and 2.0 us)
+        const double pre_us = rt == 256 ? 2.1 : 1.3, own_us = !d->cross_causal ? pre_us : rt == 256 ? 2.4 : 2.0;
+        const double unit_us = (upre * pre_us + own * own_us) / units, fixed_units = 4.0;
         // row groups and units of a batch's videos, which are below their bounds
         const double rg_mean = (double)d->num_events * per / num_videos / rt;
         const double filled = (double)tokens / num_videos / kUnitKeys + own;
@@ -217,7 +219,9 @@ Plan make_branch_plan(const pdec_dims* d, int num_videos)
             double t = rows_first ? std::max(upc + fixed_units, items * (mean_units / n + fixed_units) / kTargetItems)
                               : std::ceil(items / kTargetItems) * (upc + fixed_units);
             t *= unit_us;
-            if (n > 1) t += 4.0 + rows * n * slot_bytes / 4.0e6;
+            // the finish pass: a launch, and 0.45 ns a row or its bytes (two slots:
+            // 35000 rows 19.7 us, 117104 rows 54)
+            if (n > 1) t += 4.0 + std::max(rows * 0.45e-3, rows * n * slot_bytes / 4.0e6);
             if (best >= 0.0 && t >= best) continue;
             best = t;
             p.rows_per_item = rt;

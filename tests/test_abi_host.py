@@ -367,3 +367,9 @@ def test_a_batch_of_unequal_videos_is_cut_for_the_items_that_exist():
     info = pdec.describe_plan(d, 2)
     groups = sum(-(-e * 6 * 7 // info["rows_per_item"]) for e in (13, 2))
     assert 192 <= groups * 4 * info["max_chunks"] <= 256, info
+
+
+def test_a_causal_sequence_of_many_short_rows_is_not_cut_for_a_dear_merge():
+    """117104 rows of two slots take 54 us to merge, more than two chunks of 14638 keys at D = 64 save."""
+    d = pdec.make_dims(1, 8, 8, 64, 14638, 0, pdec.PDEC_DTYPE_BF16, queries_per_stream=14638)
+    assert pdec.describe_plan(d)["max_chunks"] == 1
