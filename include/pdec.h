@@ -486,6 +486,14 @@ int pdec_aggregate(const pdec_aggr_dims* dims, const void* g, const void* x, con
 size_t pdec_backward_workspace_size(const pdec_dims* dims);
 
 /*
+ * The kernels a pdec_attn_prefill_backward call with these dims would use, for
+ * tests and measurement: small_tiles 1 for 64-key and 64-row work-groups, 0 for
+ * 128 keys and 256 rows; the splits of the dk, dv pass over rows and of the dq
+ * pass over keys.  Each pointer may be NULL.  Host only.  Returns a pdec_status.
+ */
+int pdec_query_backward_plan(const pdec_dims* dims, int32_t* small_tiles, int32_t* row_splits, int32_t* key_splits);
+
+/*
  *   q, out, dout [E, N, H_q, D]   device, bf16, 16-byte aligned;
  *   k_prefix, v_prefix [Lmax, H_kv, D], k_event, v_event [E, cap, H_kv, D]
  *                                 device, bf16, as for the forward call;

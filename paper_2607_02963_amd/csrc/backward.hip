@@ -1,5 +1,6 @@
 // C ABI of the whole-branch attention backward (include/pdec.h): argument
-// checks, the plan of splits, and the launches of kernel_bwd.h.
+// checks, the plan of tiles and splits, and the launches of kernel_bwd.h and
+// kernel_bwd_small.h.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -8,6 +9,7 @@
 
 #include "pdec.h"
 #include "kernel_bwd.h"
+#include "kernel_bwd_small.h"
 
 namespace {
 
@@ -45,6 +47,7 @@ struct BwdPlan {
     int row_splits, key_splits, unit_per_chunk;
     long kv_elems, dq_elems;  // elements of one tensor that a split pass writes
     long part_n;              // dq splits that one prefix gradient holds
+    bool small;               // the small tiles (kernel_bwd_small.h), without splits
 };
 
 // A stage of the dk, dv pass takes about 2.4 us, a unit of the dq pass about 2.5,
@@ -102,6 +105,27 @@ BwdPlan make_plan(const pdec_dims* d)
         p.key_splits = (int)n;
     }
     p.unit_per_chunk = (int)std::min<long>(ceil_div(units, p.key_splits), 1L << 24);
+
+    // The small tiles, for calls that leave the chip idle and whose splits the
+    // output buffers do not hold.  Both times as fitted to measurements of the two
+    // (4 to 24 streams of 10 to 80 tokens over 300 to 4000 keys, five head
+    // layouts: within 10%): the launches, the longest work-group's row stages and
+    // key tiles times the rounds, and the sums of splits.
+    if (L > 0) {
+        const bool wide = d->head_dim == 128;
+        const bool split = p.row_splits > 1 || p.key_splits > 1;
+        const double split_bytes = p.row_splits > 1 ? 16.0 * p.kv_elems * p.row_splits : split ? 8.0 * p.dq_elems * p.key_splits : 0.0;
+        const double large_us = (wide ? 18.0 : 14.0) +
+                                (wide ? 1.9 : 1.2) * std::ceil(tiles * p.row_splits / cus) * ceil_div(stages, p.row_splits) +
+                                (wide ? 3.9 : 2.5) * std::ceil(groups * p.key_splits / cus) * p.unit_per_chunk +
+                                (split ? 5.0 : 0.0) + 2.2 * split_bytes / kBytesPerUs;
+        const long own_tiles = std::min<long>(E, 62 / NG + 2) * ceil_div(std::min(cap, N), 128);
+        const double kv_wgs = (ceil_div(L, 64) + E * ceil_div(cap, 64)) * H_kv, dq_wgs = ceil_div(R, 64) * H_kv;
+        const double small_us = (wide ? 7.0 : 5.0) + (wide ? 4.2 : 2.7) * ceil_div(R, 64) * std::max(1.0, kv_wgs / cus) +
+                                (wide ? 2.8 : 1.7) * (ceil_div(L, 128) + own_tiles) * std::max(1.0, dq_wgs / cus);
+        p.small = small_us < large_us;
+        if (p.small) p.row_splits = p.key_splits = 1;
+    }
     return p;
 }
 
@@ -145,14 +169,33 @@ int launch_dq(pdec::BwdArgs a, const BwdPlan& p, hipStream_t s)
 }
 
 template <int D>
+int launch_drow(const pdec::BwdArgs& a, hipStream_t s)
+{
+    const long rows = (long)a.E * a.N * a.H_q;
+    hipLaunchKernelGGL((pdec::bwd_drow_kernel<D>), dim3((unsigned)ceil_div(rows, 16)), dim3(256), 0, s, a);
+    return launch_status();
+}
+
+template <int D>
+int launch_small(const pdec::BwdArgs& a, hipStream_t s)
+{
+    int rc = launch_drow<D>(a, s);
+    if (rc != PDEC_OK) return rc;
+    const long units = ceil_div(a.Lmax, 64) + a.E * ceil_div(a.cap, 64);
+    hipLaunchKernelGGL((pdec::bwd_small_dkdv_kernel<D>), dim3((unsigned)units, a.H_kv), dim3(256), 0, s, a);
+    if ((rc = launch_status()) != PDEC_OK) return rc;
+    hipLaunchKernelGGL((pdec::bwd_small_dq_kernel<D>), dim3((unsigned)ceil_div(a.R, 64), a.H_kv), dim3(512), 0, s, a);
+    return launch_status();
+}
+
+template <int D>
 int launch(const pdec::BwdArgs& a, const BwdPlan& p, hipStream_t s)
 {
+    if (p.small) return launch_small<D>(a, s);
     int rc = PDEC_OK;
     if (p.row_splits > 1) {
         // dk, dv first, whose later splits dq holds: D in a pass of its own
-        const long rows = (long)a.E * a.N * a.H_q;
-        hipLaunchKernelGGL((pdec::bwd_drow_kernel<D>), dim3((unsigned)ceil_div(rows, 16)), dim3(256), 0, s, a);
-        rc = launch_status();
+        rc = launch_drow<D>(a, s);
         if (rc == PDEC_OK) rc = launch_dkdv<D>(a, p, s);
         if (rc == PDEC_OK) rc = launch_dq<D>(a, p, s);
     } else {
@@ -169,6 +212,17 @@ extern "C" {
 size_t pdec_backward_workspace_size(const pdec_dims* dims)
 {
     return check_dims(dims) == PDEC_OK ? workspace_for(dims) : 0;
+}
+
+int pdec_query_backward_plan(const pdec_dims* dims, int32_t* small_tiles, int32_t* row_splits, int32_t* key_splits)
+{
+    const int rc = check_dims(dims);
+    if (rc != PDEC_OK) return rc;
+    const BwdPlan p = make_plan(dims);
+    if (small_tiles) *small_tiles = p.small;
+    if (row_splits) *row_splits = p.row_splits;
+    if (key_splits) *key_splits = p.key_splits;
+    return PDEC_OK;
 }
 
 int pdec_attn_prefill_backward(const pdec_dims* dims, const void* q, const void* k_prefix, const void* v_prefix,

@@ -31,7 +31,7 @@ PATH_AUTO, PATH_VALU, PATH_MFMA, PATH_MFMA32 = 0, 1, 2, 3
 EXPORTED = ("pdec_strerror", "pdec_workspace_size", "pdec_attn_step", "pdec_attn_step_noalloc", "pdec_attn_step_ragged",
             "pdec_kv_append", "pdec_rope_kv_append", "pdec_set_path", "pdec_query_plan",
             "pdec_set_split_timer", "pdec_describe_plan", "pdec_grounding_workspace_size", "pdec_segment_grounding",
-            "pdec_aggregation_workspace_size", "pdec_aggregate", "pdec_backward_workspace_size",
+            "pdec_aggregation_workspace_size", "pdec_aggregate", "pdec_backward_workspace_size", "pdec_query_backward_plan",
             "pdec_attn_prefill_backward", "pdec_read_probe", "pdec_issue_probe", "pdec_check_lengths",
             "pdec_decode_step")
 
@@ -126,6 +126,8 @@ def lib():
         L.pdec_aggregate.argtypes = [ap, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.pdec_backward_workspace_size.restype = ctypes.c_size_t
         L.pdec_backward_workspace_size.argtypes = [dp]
+        L.pdec_query_backward_plan.restype = ctypes.c_int
+        L.pdec_query_backward_plan.argtypes = [dp] + [ctypes.POINTER(i32)] * 3
         L.pdec_attn_prefill_backward.restype = ctypes.c_int
         L.pdec_attn_prefill_backward.argtypes = [dp] + [vp] * 16 + [sz, vp]
         L.pdec_set_path.restype = ctypes.c_int
@@ -337,6 +339,13 @@ def attn_prefill(q, k_prefix, v_prefix, k_event, v_event, event_lens, prefix_len
 
 def backward_workspace_size(dims: Dims) -> int:
     return int(lib().pdec_backward_workspace_size(ctypes.byref(dims)))
+
+
+def query_backward_plan(dims: Dims):
+    """(small tiles, row splits of the dk, dv pass, key splits of the dq pass) of a backward call."""
+    v = [ctypes.c_int32() for _ in range(3)]
+    _check("pdec_query_backward_plan", lib().pdec_query_backward_plan(ctypes.byref(dims), *map(ctypes.byref, v)))
+    return v[0].value, v[1].value, v[2].value
 
 
 def attn_prefill_backward(q, k_prefix, v_prefix, k_event, v_event, event_lens, prefix_lens, out, lse, dout, *,

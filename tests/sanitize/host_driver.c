@@ -171,6 +171,7 @@ static int refusals(void)
     pdec_dims bx = dims(4, 8, 2, 128, 48, 1024, PDEC_DTYPE_BF16);
     bx.queries_per_stream = 48;
     CHECK(pdec_backward_workspace_size(&bx) > 0);
+    CHECK(pdec_query_backward_plan(&bx, NULL, NULL, NULL) == PDEC_OK);
     bx.head_dim = 96;
     CHECK(pdec_backward_workspace_size(&bx) == 0);
     /* every status has a text */

@@ -1,7 +1,8 @@
 """The backward's tiles, splits and masks at their edges, against the oracle's
 gradients: 128-key tiles and 64-row stages of dk, dv, 256-row groups and
-64-key units of dq, row splits and key splits, ended streams, caches longer
-than a branch, prefixes shorter than their bound.
+64-key units of dq, row splits and key splits, the small tiles (64 keys, 64
+rows), ended streams, caches longer than a branch, prefixes shorter than their
+bound.  Each case states the plan it is for, which is asked for first.
 
 The bar is normwise: p and ds are rounded to bf16 (2^-9 relative, random), so
 a gradient's relative error stays near 2e-3; 1e-2 leaves room for sums that
@@ -21,20 +22,31 @@ from paper_2607_02963_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # E, N, L, room, lens, H_q, H_kv, D, cap
-    (1, 1, 1, 1, [1], 1, 1, 128, 1),                        # one row, one prefix key, one own key
-    (1, 129, 0, 0, [129], 7, 1, 128, 129),                  # pure causal, a key past one tile, row splits
-    (2, 200, 0, 0, [200, 150], 4, 1, 64, 260),              # caches longer than the branch; two streams
-    (3, 64, 128, 128, [64, 0, 64], 4, 4, 128, 64),          # 192 rows: a full tile of keys, an ended stream
-    (5, 52, 257, 300, [52, 3, 52, 52, 0], 5, 1, 128, 64),   # 1300 rows over few keys: row splits; a short prefix
-    (2, 5, 4000, 4100, [5, 4], 6, 2, 128, 5),               # few rows over many keys: key splits
-    (7, 9, 1000, 1000, [9, 9, 0, 9, 1, 9, 9], 3, 3, 64, 9), # several streams in a row group
+    # E, N, L, room, lens, H_q, H_kv, D, cap, plan: tiles, row splits above 1, key splits above 1
+    (1, 1, 1, 1, [1], 1, 1, 128, 1, "small"),                        # one row, one prefix key, one own key
+    (1, 129, 0, 0, [129], 7, 1, 128, 129, "large rows"),             # pure causal, a key past one tile
+    (2, 200, 0, 0, [200, 150], 4, 1, 64, 260, "large"),              # caches longer than the branch; two streams
+    (3, 64, 128, 128, [64, 0, 64], 4, 4, 128, 64, "small"),          # 192 rows: full tiles, an ended stream
+    (5, 52, 257, 300, [52, 3, 52, 52, 0], 5, 1, 128, 64, "large rows"),    # many rows over few keys; a short prefix
+    (2, 5, 4000, 4100, [5, 4], 6, 2, 128, 5, "large keys"),          # few rows over many keys
+    (7, 9, 1000, 1000, [9, 9, 0, 9, 1, 9, 9], 3, 3, 64, 9, "large keys"),  # several streams in a row group
+    (2, 40, 128, 128, [40, 33], 7, 1, 128, 40, "large"),             # 280 rows and a prefix, unsplit; two row groups
+    (5, 64, 128, 130, [64, 0, 63, 1, 64], 4, 2, 128, 70, "small"),         # two keys past a tile that hold nothing
+    (4, 30, 130, 200, [30, 0, 17, 30], 6, 6, 64, 40, "small"),       # D = 64; a prefix past two units; caches longer
+    (9, 11, 320, 320, [11, 11, 3, 0, 11, 11, 11, 1, 11], 28, 4, 128, 11, "small"),  # several streams in a row tile
 ]
+
+
+def _plan(E, N, room, H_q, H_kv, D, cap):
+    small, rows, keys = pdec.query_backward_plan(
+        pdec.make_dims(E, H_q, H_kv, D, cap, room, pdec.PDEC_DTYPE_BF16, queries_per_stream=N))
+    return ("small" if small else "large") + (" rows" if rows > 1 else "") + (" keys" if keys > 1 else "")
 
 
 @pytest.mark.parametrize("case", CASES, ids=[f"E{c[0]}N{c[1]}L{c[2]}d{c[7]}" for c in CASES])
 def test_backward_edges_match_oracle(case):
-    E, N, L, room, lens, H_q, H_kv, D, cap = case
+    E, N, L, room, lens, H_q, H_kv, D, cap, plan = case
+    assert _plan(E, N, room, H_q, H_kv, D, cap) == plan
     rng = np.random.default_rng(300 + E + N + L)
     f = lambda s, *shape: wl.bf16_bits((s * rng.standard_normal(shape)).astype(np.float32))  # noqa: E731
     q, kp, vp = f(1.2, E, N, H_q, D), f(1.0, room, H_kv, D), f(0.5, room, H_kv, D)
