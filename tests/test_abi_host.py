@@ -113,7 +113,7 @@ def test_tail_pass_plan():
                                             (1, 1, pdec.PDEC_DTYPE_BF16, pdec.PATH_MFMA),
                                             (4, 4, pdec.PDEC_DTYPE_F32, pdec.PATH_VALU)])
 def test_dispatch_rule(E, G, dt, expect):
-    """bf16 -> matrix core at any row count, float32 -> vector ALUs."""
+    """bf16 -> the bf16 matrix-core kernels at any row count (path 2), float32 -> its own kernel, which reports path 1."""
     d = _dims(num_events=E, H_q=G, H_kv=1, dtype_code=dt)
     assert pdec.query_plan(d)[0] == expect
 

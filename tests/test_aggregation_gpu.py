@@ -157,8 +157,8 @@ def test_aggregation_explicit_scale():
 @pytest.mark.parametrize("S,hidden", [(15, 504), (16, 512), (17, 520), (64, 1032), (257, 2056), (4097, 64)])
 def test_aggregation_many_salient_segments(S, hidden):
     """Every count of listed segments left over by four waves of four loads,
-    lists longer than one 256-entry batch, 64-vector slices with a remainder,
-    and segment counts at the edges of the 64-way search."""
+    lists longer than one 256-entry batch, and 64-vector slices with a
+    remainder."""
     sizes = np.random.default_rng(S).integers(0, 3, S).tolist()
     sizes[-1] += 300  # five or six chunks: a remainder of the four pieces in flight
     w = wl.make_aggregation(K=20, N=sum(sizes), S=S, hidden=hidden, H_q=4, H_kv=2, D=64, seed=S, sizes=sizes, max_run=6)

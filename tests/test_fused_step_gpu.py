@@ -3,7 +3,8 @@ calls it replaces, pdec_kv_append then the step, on the same inputs: out,
 lse, both caches and the advanced counts must agree bit for bit.  The cases
 reach every kernel family the fused call can take (the 256-, 128- and
 64-row matrix-core shapes, the latter with a single stream's 7 rows per kv
-head, the bf16 and f32 vector kernels), a ragged batch,
+head, the bf16 vector kernel, the float32 kernel's 16- and 32-row forms, the
+latter with the appended row in a unit requested ahead), a ragged batch,
 a step whose single chunk writes the result itself, and a step in which
 nothing is attended; streams that have ended, full caches and empty caches
 are mixed in.  The two-call result is itself checked against the oracle by
@@ -28,6 +29,7 @@ CASES = {
     "valu_bf16_forced_E1": ("bf16", (2000,), (1,), 28, 4, 128, 24, 1),
     "valu_bf16_forced_E9": ("bf16", (900,), (9,), 28, 4, 128, 24, 1),
     "valu_f32_E4": ("f32", (700,), (4,), 8, 2, 128, 16, 0),
+    "f32_long_chunks_E40": ("f32", (2000,), (40,), 28, 4, 128, 70, 0),
     "ragged_3": ("bf16", (1800, 0, 640), (9, 3, 20), 28, 4, 128, 24, 0),
     "one_chunk_E1024": ("bf16", (64,), (1024,), 64, 8, 128, 8, 0),
     "nothing_attended": ("bf16", (0,), (5,), 8, 2, 128, 8, 0),
@@ -99,6 +101,10 @@ def test_fused_step_is_bitwise_append_then_step(name):
     if name == "one_chunk_E1024":  # the split pass writes out and lse itself
         dims = pdec.make_dims(s.num_events, s.H_q, s.H_kv, s.D, s.cap, int(s.prefix_lens[0]), pdec._dtype_code(d["q"]))
         assert pdec.describe_plan(dims)["merge_pass"] == 0
+    if name == "f32_long_chunks_E40":  # prefix and own units of several streams in one chunk
+        dims = pdec.make_dims(s.num_events, s.H_q, s.H_kv, s.D, s.cap, int(s.prefix_lens[0]), pdec._dtype_code(d["q"]))
+        info = pdec.describe_plan(dims)
+        assert info["rows_per_item"] == 32 and info["chunk_keys"] >= 4 * 64
     prev = pdec.set_path(path)
     try:
         ref = _two_calls(s, d, lens_in, live, kn, vn)
