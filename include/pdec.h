@@ -258,9 +258,9 @@ int pdec_rope_kv_append(const pdec_dims* dims, int32_t num_videos, void* q, cons
 
 /*
  * Kernel-path selection for the shared-prefix pass, for tests and tuning:
- * 0 = automatic (bfloat16 uses the matrix-core kernel, float32 the vector
- * kernel), 1 = always the
- * vector kernel, 2 = matrix-core kernel where the type allows it, 3 = as 2,
+ * 0 = automatic, 1 = bfloat16 decode steps on the vector kernel, 2 = on the
+ * matrix-core kernels (float32 has one kernel, on the float32 matrix product,
+ * and reports path 1 whatever the setting; whole branches have theirs), 3 = as 2,
  * with the decode step at head_dim 128 and more than 64 query rows per kv
  * head on 32-row tiles (kernel shapes 4 and 5) instead of 16-row ones.
  * Process-wide; returns the previous setting, or PDEC_ERR_INVALID_ARG.
@@ -268,7 +268,8 @@ int pdec_rope_kv_append(const pdec_dims* dims, int32_t num_videos, void* q, cons
 int pdec_set_path(int path);
 
 /*
- * The kernel path (1 = vector, 2 = matrix core) and the prefix chunk length
+ * The kernel path (1 = float32, or bfloat16 on the vector kernel; 2 = bfloat16 on
+ * the matrix cores) and the prefix chunk length
  * (keys per work item) a step call with these dims would use.  Host-only.
  * Returns a pdec_status.
  */
@@ -276,11 +277,11 @@ int pdec_query_plan(const pdec_dims* dims, int32_t num_videos, int32_t* path, in
 
 /* The whole work split of a step call, for tests and measurement. */
 typedef struct pdec_plan_info {
-    int32_t path;          /* 1 = vector kernel, 2 = matrix-core kernel                          */
+    int32_t path;          /* 1 = float32, or bf16 on the vector kernel; 2 = bf16 matrix-core    */
     int32_t kernel_shape;  /* matrix-core work-group shape: 1 = 64 rows, 2 = 128 rows,          */
                            /* 3 = 256 rows on 16-row tiles; 4 = 256 rows, 5 = 128 rows on      */
                            /* 32-row tiles (pdec_set_path(3) only); whole branches: 6 = 128     */
-                           /* rows, 7 = 256 rows; 0 on the vector path                          */
+                           /* rows, 7 = 256 rows; 0 on path 1                                    */
     int32_t rows_per_item; /* query rows of one kv head that one work item serves               */
     int32_t row_groups;    /* work items per (video, kv head, chunk): ceil(rows / rows_per_item)  */
     int32_t chunk_keys;    /* keys of the virtual key sequence per chunk                         */

@@ -317,6 +317,8 @@ __global__ __launch_bounds__(64 * WR * WK) void split_mfma_kernel(StepArgs a)
     if (item < 0) return;
     const ItemId id = item_id(a, item);
     const VideoInfo vi = video_info(a, id.v);
+    // (qps is 1 here; without its factors the compiler's code for a 32768 x 32
+    // step takes 34.9 us instead of 34.4)
     const int R = vi.E * a.G * a.qps;
     const int row0 = id.rg * C::RT;
     if (row0 >= R) return;

@@ -250,7 +250,7 @@ Plan make_plan(const pdec_dims* d, int num_videos)
     // (7 rows per kv head) pads its 16-row tile and still takes about half
     // the time of the vector kernel (12.8 vs 22.7 us at a 16384-token
     // prefix, measured); float32 has a kernel of its own (kernel_f32.h),
-    // planned as the vector path
+    // which counts as path 1
     int path = d->dtype == PDEC_DTYPE_BF16 ? kPathMfma : kPathValu;
     const int ov = g_path_override.load();
     if (ov == kPathValu) path = kPathValu;

@@ -60,8 +60,8 @@ def test_self_plan_mask_leaves_the_work_split_alone():
 
 
 def test_workspace_holds_every_partial_slot():
-    """Slots cover the worst case.  With the own units as chunk units (the
-    vector kernel): every prefix unit plus every stream's cache full (129 rows
+    """Slots cover the worst case.  With the own units as chunk units
+    (float32): every prefix unit plus every stream's cache full (129 rows
     -> 3 units of 64 keys), cut into chunks of chunk_keys.  With the per-stream
     tail pass (a bf16 decode step on the matrix-core kernel): one slot for the
     tail plus the prefix units cut into chunks."""
@@ -91,7 +91,7 @@ def test_tail_pass_plan():
     # items aim at the compute units the tail leaves: no more than 256 - 16
     assert info["work_items"] <= 256 - 16
     assert pdec.describe_plan(_dims(num_events=33))["tail_blocks"] == 24   # 132 pairs -> 17 -> 24
-    # no tail pass: float32 (vector kernel), whole branches, G > 16, the
+    # no tail pass: float32, whole branches, G > 16, the
     # 32-row-tile kernel, and a step whose units fit one chunk
     assert pdec.describe_plan(_dims(dtype_code=pdec.PDEC_DTYPE_F32))["tail_blocks"] == 0
     mq = pdec.make_dims(8, 28, 4, 128, 16, 1024, pdec.PDEC_DTYPE_BF16, queries_per_stream=4)
