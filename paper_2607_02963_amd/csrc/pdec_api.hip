@@ -206,7 +206,10 @@ Plan make_branch_plan(const pdec_dims* d, int num_videos)
         const double rg_mean = (double)d->num_events * per / num_videos / rt;
         const double filled = (double)tokens / num_videos / kUnitKeys + own;
         for (long n = 1; n <= std::min<long>(units, kMaxChunks); ++n) {
-            // no more states than the scratch of pdec_attn_step_noalloc holds
+            // No more states than the scratch of pdec_attn_step_noalloc holds, so that
+            // it takes every call that fits it in one chunk.  The plan is the one of
+            // callers with a workspace of their own too: above some 63000 rows at
+            // D = 128 they get one chunk, also where a second would fill a round.
             if (n > 1 && n * rows * slot_bytes + num_videos * 4.0 > (double)PDEC_NOALLOC_SCRATCH_BYTES) break;
             const long upc = ceil_div(units, n);
             if (ceil_div(units, upc) != n) continue;  // fewer chunks of the same length do
