@@ -740,7 +740,7 @@ def run_prefill_backward(args, torch, pdec, wl):
                    "tokens_per_branch": N, "H_q": H_q, "H_kv": H_kv, "head_dim": D},
         "roofline": {"bound": "mfma", "achieved": round(tflops, 1), "peak": 2500.0, "unit": "TFLOP/s",
                      "frac": round(tflops / 2500.0, 4), "traffic": None,
-                     "kernel": "bwd_drow + bwd_dkdv + bwd_dq (per call)", "kernel_us": round(us, 1),
+                     "kernel": "the dq and dk, dv passes and the sum of splits (per call)", "kernel_us": round(us, 1),
                      "kernel_algorithmic_flops": flops},
     }
     print(json.dumps(rec), flush=True)
